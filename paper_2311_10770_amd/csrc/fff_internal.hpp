@@ -142,6 +142,7 @@ struct Plan {
     int split_level = 0;           // grouped mode
     int walk_affine = 0;           // grouped / tiled: one tree per walk workgroup, by XCD
     int tile_pair = 0;             // tiled: a tile workgroup per pair of sibling leaves
+    int dense = 0;                 // tiled: subtrees as dense products (fff_dense.hip) instead of walk and leaf tiles
     int cu_count = 0;              // masked: compute units, for the products' tile choice
     const char* name = "";
 };
@@ -180,6 +181,12 @@ hipError_t run_stack(const StackParams& sp, const Plan& plan, hipStream_t stream
 size_t grouped_workspace_bytes(int64_t n_tokens, int32_t depth, int32_t n_trees, int32_t split_level);
 // Tiled mode scratch (grouped scratch plus the leaf buckets); 0 when the shape has no tiled mode.
 size_t tiled_workspace_bytes(int64_t n_tokens, int32_t depth, int32_t n_trees, int32_t hidden);
+// The dense form of tiled mode (fff_dense.hip): whether a validated tiled request has it, the levels
+// of its top pass (0: none), its scratch (less than the leaf buckets') and the launch.
+bool dense_shape(const Params& p);
+int dense_top_levels(int32_t depth);
+size_t dense_workspace_bytes(int64_t n_tokens);
+hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t stream);
 // Split level used when the caller asks for the default (0 in fff_args).
 int default_split_level(int32_t depth, int32_t n_trees);
 

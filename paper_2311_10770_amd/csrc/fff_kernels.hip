@@ -1297,6 +1297,26 @@ static bool tile_pairs(const Params& p) {
     return p.depth >= 5 && p.depth + 2 <= 4 * TILE_MAX_STEPS && p.n_tokens < (int64_t(16) << p.depth);
 }
 
+// Subtrees as dense products (fff_dense.hip): its two passes cost about 30 us whatever the batch, so
+// it takes large ones: at depth 10 and 11 from 49152 tokens, shallower from 64 per leaf (where the tile
+// launch has few workgroups) and 4096.  Measured against the walk and the leaf tiles (bf16, buffers
+// rotating, us; hidden 768): depth 11, 40000 / 49152 / 65536 / 131072 tokens 64 / 66 / 82 / 162 against
+// 63 / 77 / 95 / 174 (hidden 1024, 65536: 101 against 124); depth 10, 49152 / 65536 / 262144: 67 / 78 /
+// 311 against 70 / 87 / 305; depth 9, 16384 / 32768 / 65536: 35 / 46 / 73 against 33 / 54 / 91; depth
+// 7, 4096 / 8192: 31 / 32 against 23 / 36; depth 5, 2048 / 4096: 24 / 24 against 22 / 31.  Not between
+// 81920 tokens (one more would start a second round of subtree workgroups) and 98304 (two pairs of
+// passes): depth 11, 90000 tokens 126 against 122.
+constexpr int64_t DENSE_TOKENS = 49152, DENSE_ROUND = 81920, DENSE_TWO = 98304;
+constexpr int64_t DENSE_MIN_TOKENS = 4096, DENSE_PER_LEAF = 64;
+static bool dense_plan(const Params& p) {
+    const int64_t n = p.n_tokens;
+    const bool one = n <= DENSE_ROUND, two = n >= DENSE_TWO;
+    const bool big = n >= DENSE_TOKENS && (one || (two && p.depth >= 11));
+    const bool full = n >= DENSE_MIN_TOKENS && n >= (DENSE_PER_LEAF << p.depth) && (one || (two && p.depth <= 8));
+    return dense_shape(p) && (big || full) &&
+           dense_workspace_bytes(n) <= tiled_workspace_bytes(n, p.depth, p.n_trees, p.hidden);
+}
+
 // The walk launch of the grouped and tiled plans: with 2, 4 or 8 trees one tree per workgroup
 // (by XCD), whose top levels then get the whole LDS budget; otherwise every tree per token.
 static bool plan_walk(const Params& p, const Variant& v, int lds_levels_req, const DeviceInfo& dev, Plan* plan,
@@ -1435,6 +1455,10 @@ int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_
         plan->emit_lanes = v->emit_lanes;
         plan->split_level = std::min<int>(p.depth - 2, 5);  // subtrees of at least four leaves
         plan->name = v->name;
+        plan->tile_pair = tile_pairs(p) ? 1 : 0;
+        plan->dense = dense_plan(p);
+        plan->cu_count = dev.cu_count;
+        if (plan->dense) return ST_OK;
         const int64_t leaves = int64_t(1) << p.depth;
         Launch& F = plan->launch[plan->n_launch++];
         F.kernel = reinterpret_cast<const void*>(&fill_i32_kernel);
@@ -1443,7 +1467,6 @@ int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_
         Launch& W = plan->launch[plan->n_launch++];
         if (!plan_walk(p, *v, lds_levels_req, dev, plan, W)) return ST_UNSUPPORTED;
         Launch& E = plan->launch[plan->n_launch++];
-        plan->tile_pair = tile_pairs(p) ? 1 : 0;
         E.kernel = tile_kernel_for(*v, p, 0, plan->tile_pair);  // the first tree's; run_forward picks each tree's form
         E.block = 64 * tile_waves(p.hidden);
         // per tree: one workgroup per leaf or pair of leaves (a multiple of eight: leaves >= 32), then
@@ -1592,6 +1615,7 @@ hipError_t run_forward(const Params& p, const Plan& plan, void* workspace, size_
                        hipStream_t stream) {
     if (plan.kind == KIND_MASKED) return run_masked(p, workspace, plan.cu_count, stream);
     if (plan.kind == KIND_SUBTREE) return run_subtree(p, plan.launch[0].grid, stream);
+    if (plan.kind == KIND_TILED && plan.dense) return run_dense(p, workspace, plan.cu_count, stream);
     Params q = p;
     q.lds_levels = plan.lds_levels;
     q.walk_affine = plan.walk_affine;

@@ -960,3 +960,115 @@ def test_masked_bits_do_not_depend_on_the_process():
         assert r.returncode == 0, r.stderr[-2000:]
         runs.append(r.stdout.strip().splitlines()[-1])
     assert runs[0] == runs[1], runs
+
+
+# ----------------------------------------------------------------- tiled mode, subtrees as dense products
+
+
+def dense_of(fff, x, wi, wo, D, **kw):
+    return int(fff.describe(x, wi, wo, D, 1, mode="tiled", **kw).split("dense=")[1].split()[0])
+
+
+@pytest.mark.parametrize("H,D,B", [
+    (768, 5, 4096), (768, 5, 5003),       # one pass: the whole tree is the subtree
+    (768, 6, 4099), (768, 7, 8207),       # few and unevenly filled groups
+    (128, 8, 16385), (896, 9, 32769),     # one column block; an odd number of them
+    (1024, 10, 49153), (768, 11, 50021),  # five and six levels below six
+    (1024, 11, 49152)])
+def test_tiled_dense(fff_lib, H, D, B):
+    """The dense form against the oracle: ragged last tiles and workgroups, every split of the levels."""
+    if H in (128, 896):  # no tiled plan at these widths: refused, whatever the batch
+        with pytest.raises(fff_lib.FffError):
+            run_fff(fff_lib, layer(300, 64, H, D, 1, "bf16", "bf16"), D, 1, "bf16", mode="tiled")
+        H = 1024 if H == 896 else 768
+    L = layer(300 + D, B, H, D, 1, "bf16", "bf16")
+    x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
+    assert dense_of(fff_lib, x, wi, wo, D) == 1
+    check_layer(fff_lib, f"tiled dense H={H} B={B} D={D}", L, D, 1, "bf16", mode="tiled")
+
+
+def test_tiled_dense_plan(fff_lib):
+    """From 49152 tokens, or 64 per leaf and 4096, with a gap where a second round would start; bf16 x, W
+    and y only."""
+    w = torch.zeros(1, 4095, 768, dtype=torch.bfloat16, device=DEV)
+    x = torch.zeros(49152, 768, dtype=torch.bfloat16, device=DEV)
+    assert dense_of(fff_lib, x, w, w, 11) == 1 and dense_of(fff_lib, x[:49151], w, w, 11) == 0
+    w7 = w[:, :255].contiguous()
+    assert dense_of(fff_lib, x[:8192], w7, w7, 7) == 1 and dense_of(fff_lib, x[:8191], w7, w7, 7) == 0
+    w5 = w[:, :63].contiguous()
+    assert dense_of(fff_lib, x[:4096], w5, w5, 5) == 1 and dense_of(fff_lib, x[:4095], w5, w5, 5) == 0
+    assert dense_of(fff_lib, x, w, w, 11, y_dtype=torch.float32) == 0
+    assert dense_of(fff_lib, x.float(), w, w, 11, y_dtype=torch.bfloat16) == 0
+    assert dense_of(fff_lib, x, w, w, 11, norm="layernorm") == 0
+    big = torch.zeros(131072, 768, dtype=torch.bfloat16, device=DEV)
+    w10 = w[:, :2047].contiguous()
+    for n, d11, d10, d7 in ((81920, 1, 1, 1), (81921, 0, 0, 0), (98303, 0, 0, 0), (98304, 1, 0, 1), (131072, 1, 0, 1)):
+        assert (dense_of(fff_lib, big[:n], w, w, 11), dense_of(fff_lib, big[:n], w10, w10, 10),
+                dense_of(fff_lib, big[:n], w7, w7, 7)) == (d11, d10, d7), n
+    w12 = torch.zeros(1, 8191, 768, dtype=torch.bfloat16, device=DEV)
+    assert dense_of(fff_lib, x, w12, w12, 12) == 0
+
+
+@pytest.mark.parametrize("D,B", [(5, 4100), (11, 49200)])
+@pytest.mark.parametrize("out", ["residual", "accumulate", "in place"])
+def test_tiled_dense_output_modes(fff_lib, D, B, out):
+    L = layer(310 + D, B, 768, D, 1, "bf16", "bf16")
+    y0 = L["x"] if out == "in place" else synth.make_x(311, B, 768, "bf16")
+    if out == "in place":
+        y = fff_lib.from_numpy(L["x"], DEV)
+        wi, wo = fff_lib.from_numpy(L["w_in"], DEV), fff_lib.from_numpy(L["w_out"], DEV)
+        nodes = torch.empty((B, 1, D + 1), dtype=torch.int32, device=DEV)
+        fff_lib.forward(y, wi, wo, D, 1, y, nodes_out=nodes, mode="tiled", out="residual")
+        got = {"y": fff_lib.to_numpy(y), "nodes": nodes.cpu().numpy()}
+    else:
+        got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", out=out, y_init=y0 if out == "accumulate" else None)
+    ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
+    parity.assert_parity(L["x"], L["w_in"], L["w_out"], D, 1, ref, got["y"], got["nodes"], tol=2e-2,
+                         base_dev=y0 if out == "accumulate" else L["x"])
+
+
+def test_tiled_dense_token_chunks(fff_lib):
+    """More tokens than one pair of passes takes (98304): chunks of equal size, every row written."""
+    L = layer(320, 100003, 768, 6, 1, "bf16", "bf16")
+    check_layer(fff_lib, "tiled dense chunks", L, 6, 1, "bf16", mode="tiled")
+
+
+def test_tiled_dense_skewed_routing_deterministic(fff_lib):
+    """Clustered tokens: a few groups hold most tokens, others none; two runs give the same bits, and a
+    token's row does not depend on which tokens share its batch."""
+    B, D = 60000, 11
+    x = synth.make_clustered_x(330, B, 768, "bf16", n_centres=5)
+    wi, wo = synth.make_weights(330, 768, D, 1, "bf16")
+    L = {"x": x, "w_in": wi, "w_out": wo}
+    check_layer(fff_lib, "tiled dense clustered", L, D, 1, "bf16", mode="tiled")
+    a = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled")
+    b = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled")
+    assert np.array_equal(a["y"], b["y"]) and np.array_equal(a["nodes"], b["nodes"])
+    c = run_fff(fff_lib, dict(L, x=np.ascontiguousarray(x[1001:51001])), D, 1, "bf16", mode="tiled")
+    assert np.array_equal(a["y"][1001:51001], c["y"]) and np.array_equal(a["logits"][1001:51001], c["logits"])
+
+
+@pytest.mark.parametrize("D,B", [(5, 4300), (11, 50000)])
+def test_tiled_dense_non_finite_weights(fff_lib, D, B):
+    """A node no token visits may hold anything (here nan and inf in both matrices): the outputs are
+    those of the visited nodes.  A visited node's inf reaches its own tokens only."""
+    L = layer(340 + D, B, 768, D, 1, "bf16", "bf16")
+    ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
+    leaf = ref["nodes"][0, 0, D]
+    keep = ref["nodes"][:, 0, D] != leaf
+    L["x"] = np.ascontiguousarray(L["x"][keep])
+    ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
+    assert dense_of(fff_lib, *(fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out")), D) == 1
+    bad = {k: L[k].copy() for k in ("w_in", "w_out")}
+    bad["w_in"][0, leaf] = 0x7FC0       # nan
+    bad["w_out"][0, leaf, ::2] = 0x7F80  # inf
+    bad["w_out"][0, leaf, 1::2] = 0xFFC0
+    got = run_fff(fff_lib, dict(L, **bad), D, 1, "bf16", mode="tiled")
+    parity.assert_parity(L["x"], L["w_in"], L["w_out"], D, 1, ref, got["y"], got["nodes"], tol=2e-2)
+    visited = ref["nodes"][5, 0, D]
+    one = {"w_in": L["w_in"], "w_out": L["w_out"].copy()}
+    one["w_out"][0, visited, 7] = 0x7F80
+    got = run_fff(fff_lib, dict(L, **one), D, 1, "bf16", mode="tiled")
+    finite = np.isfinite(synth.bf16_bits_to_f32(got["y"]))
+    hit = got["nodes"][:, 0, D] == visited
+    assert hit.any() and not finite[hit, 7].any() and finite[~hit].all() and np.delete(finite[hit], 7, axis=1).all()
