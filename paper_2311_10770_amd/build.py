@@ -31,7 +31,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-fvi
 
 LIBS = {
     "libfff.so": {"sources": ["fff_api.cpp", "fff_kernels.hip", "fff_backward.hip", "fff_masked.hip", "fff_gemm.hip",
-                              "fff_subtree.hip", "fff_dense.hip"],
+                              "fff_subtree.hip", "fff_dense.hip",
+                              "fff_wide.hip"],
                   "link": []},
     "libfffbench.so": {"sources": ["bench_helpers.hip"], "link": ["-L/opt/rocm/lib", "-lhipblaslt"]},
 }

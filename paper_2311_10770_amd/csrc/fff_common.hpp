@@ -322,6 +322,22 @@ struct LevelRegs {
     }
 };
 
+// Per-visit records (optional outputs): node and logit of every level.
+template <int LANES>
+__device__ __forceinline__ void write_records(int32_t* nodes, float* logits, const Params& p,
+                                              const LevelRegs<LANES>& lv, uint32_t leaf1, int64_t tok, int t, int sl) {
+    const int D = p.depth;
+#pragma unroll
+    for (int r = 0; r < LevelRegs<LANES>::NR; ++r) {
+        const int l = r * LANES + sl;
+        if (l <= D) {
+            const int64_t rec = (tok * p.n_trees + t) * (D + 1) + l;
+            if (nodes) nodes[rec] = int32_t((leaf1 >> (D - l)) - 1);
+            if (logits) logits[rec] = lv.v[r];
+        }
+    }
+}
+
 // Phase 1 of one tree: the CMM walk from the root, reading only W_in rows.
 // Levels below KD come from LDS rows (lrows + node*lstride, already offset by
 // the lane), the rest from global rows (win + node*ROWV).  Level logits are

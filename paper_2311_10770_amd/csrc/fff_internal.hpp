@@ -143,6 +143,7 @@ struct Plan {
     int walk_affine = 0;           // grouped / tiled: one tree per walk workgroup, by XCD
     int tile_pair = 0;             // tiled: a tile workgroup per pair of sibling leaves
     int dense = 0;                 // tiled: subtrees as dense products (fff_dense.hip) instead of walk and leaf tiles
+    int wide_vecs = 0;             // generic, rows of whole 16-byte vectors: vectors per row
     int cu_count = 0;              // masked: compute units, for the products' tile choice
     const char* name = "";
 };
@@ -187,6 +188,16 @@ bool dense_shape(const Params& p);
 int dense_top_levels(int32_t depth);
 size_t dense_workspace_bytes(int64_t n_tokens);
 hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t stream);
+// GENERIC for rows of whole 16-byte vectors (fff_wide.hip): the kernel for p's row length and types;
+// false where it does not apply.
+struct WidePlan {
+    const void* kernel;
+    int rowv;      // vectors per W row
+    int row_vecs;  // vectors per row in LDS
+    int lanes;     // per token
+    int block;
+};
+bool wide_plan(const Params& p, WidePlan* w);
 // Split level used when the caller asks for the default (0 in fff_args).
 int default_split_level(int32_t depth, int32_t n_trees);
 

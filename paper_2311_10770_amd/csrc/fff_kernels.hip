@@ -21,7 +21,8 @@
 //   grouped by their tree-0 node at level k and every subtree is emitted by
 //   workgroups of one XCD (blockIdx % 8), so the subtree's W_out rows stay in
 //   that XCD's L2 instead of being fetched by all eight.
-// GENERIC (generic_kernel): any hidden size, one wave per token.
+// GENERIC: any hidden size; rows of whole 16-byte vectors as the fused descent with a run-time row
+//   length (fff_wide.hip), others one wave per token (generic_kernel).
 #include "fff_common.hpp"
 #include "fff_device.hpp"
 #include "fff_internal.hpp"
@@ -54,22 +55,6 @@ __device__ __forceinline__ void stage_rows(uint4* lds, const void* w, int T, int
         const int64_t tn = i / ROWV;
         const int64_t t = tn / Nk, node = tn % Nk;
         lds[tn * stride + off + v] = src[(t * N + node) * ROWV + v];
-    }
-}
-
-// Per-visit records (optional outputs): node and logit of every level.
-template <int LANES>
-__device__ __forceinline__ void write_records(int32_t* nodes, float* logits, const Params& p,
-                                              const LevelRegs<LANES>& lv, uint32_t leaf1, int64_t tok, int t, int sl) {
-    const int D = p.depth;
-#pragma unroll
-    for (int r = 0; r < LevelRegs<LANES>::NR; ++r) {
-        const int l = r * LANES + sl;
-        if (l <= D) {
-            const int64_t rec = (tok * p.n_trees + t) * (D + 1) + l;
-            if (nodes) nodes[rec] = int32_t((leaf1 >> (D - l)) - 1);
-            if (logits) logits[rec] = lv.v[r];
-        }
     }
 }
 
@@ -959,7 +944,7 @@ __global__ __launch_bounds__(BLOCK) void stack_kernel(StackParams sp) {
 }
 
 // ----------------------------------------------------------------------------
-// generic kernel (any hidden size)
+// generic kernel (any hidden size; rows that are not whole 16-byte vectors, or very large matrices)
 // ----------------------------------------------------------------------------
 
 template <bool BF>
@@ -1521,6 +1506,25 @@ int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_
     const int pairs = p.n_trees * (p.depth + 1);
     if (pairs > GENERIC_MAX_PAIRS) return ST_UNSUPPORTED;
     plan->kind = KIND_GENERIC;
+    WidePlan wide;
+    if (wide_plan(p, &wide)) {
+        plan->wide_vecs = wide.rowv;
+        plan->lanes = wide.lanes;
+        plan->name = "vector rows";
+        // top levels of all trees in LDS, W_in and W_out rows, as in the fused descent
+        const size_t row = size_t(wide.row_vecs) * 16;
+        auto bytes = [&](int k) { return size_t(p.n_trees) * ((size_t(1) << k) - 1) * 2 * row; };
+        int k = 0;
+        while (k < p.depth + 1 && bytes(k + 1) <= DESCENT_LDS_BUDGET) ++k;
+        plan->lds_levels = k;
+        Launch& L = plan->launch[plan->n_launch++];
+        L.kernel = wide.kernel;
+        L.block = wide.block;
+        L.lds_bytes = bytes(k);
+        const int64_t per = wide.block / wide.lanes;
+        L.grid = resident_grid(dev, L.kernel, L.lds_bytes, (p.n_tokens + per - 1) / per, wide.block);
+        return ST_OK;
+    }
     plan->lanes = 64;
     plan->name = "wave per token";
     Launch& L = plan->launch[plan->n_launch++];
@@ -1648,7 +1652,8 @@ hipError_t run_forward(const Params& p, const Plan& plan, void* workspace, size_
     for (int i = 0; i < plan.n_launch; ++i) {
         const Launch& L = plan.launch[i];
         if (plan.kind == KIND_GROUPED && i == 1) q.lds_levels = plan.emit_lds_levels;
-        void* args[] = {&q};
+        int rowv = plan.wide_vecs;  // the second argument of GENERIC's vector-row kernel only
+        void* args[] = {&q, &rowv};
         const hipError_t e = hipLaunchKernel(L.kernel, dim3(L.grid), dim3(L.block), args, L.lds_bytes, stream);
         if (e != hipSuccess) return e;
     }

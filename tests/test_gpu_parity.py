@@ -1072,3 +1072,42 @@ def test_tiled_dense_non_finite_weights(fff_lib, D, B):
     finite = np.isfinite(synth.bf16_bits_to_f32(got["y"]))
     hit = got["nodes"][:, 0, D] == visited
     assert hit.any() and not finite[hit, 7].any() and finite[~hit].all() and np.delete(finite[hit], 7, axis=1).all()
+
+
+# ----------------------------------------------------------------- generic mode, rows of whole vectors
+
+
+@pytest.mark.parametrize("xd,wd,H", [
+    ("bf16", "bf16", h) for h in (8, 248, 256, 264, 512, 520, 768, 776, 1024, 1032, 1536, 1544, 2048, 2056, 3080, 4088, 4104)
+] + [("f32", "bf16", h) for h in (16, 264, 520, 1032, 1544, 2056, 3080, 4096)
+] + [("f32", "f32", h) for h in (4, 132, 260, 300, 388, 516, 772, 1028, 1540, 2044, 2052)
+] + [("bf16", "f32", h) for h in (4, 300, 1028)])
+def test_generic_vector_rows(fff_lib, xd, wd, H):
+    """Widths on both sides of every lane layout's capacity, partly filled last vectors, and the first
+    width past the layouts; two trees, ragged tokens, records."""
+    for B, D in ((7, 3), (301, 6)):
+        L = layer(400 + H, B, H, D, 2, xd, wd)
+        check_layer(fff_lib, f"generic vectors {xd}/{wd} H={H}", L, D, 2, "f32", mode="generic")
+
+
+@pytest.mark.parametrize("xd,wd,yd,H", [("bf16", "bf16", "bf16", 520), ("f32", "bf16", "f32", 264), ("f32", "f32", "f32", 300),
+                                        ("bf16", "f32", "bf16", 388)])
+def test_generic_vector_rows_block(fff_lib, xd, wd, yd, H):
+    """LayerNorm (gain and shift, and without either), residual and accumulate."""
+    B, D = 77, 5
+    L = layer(410 + H, B, H, D, 1, xd, wd)
+    gamma, beta = synth.make_norm(410, H)
+    x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
+    for norm in ({"gamma": gamma, "beta": beta, "eps": 1e-5}, {"eps": 1e-5}):
+        nodes = torch.empty((B, 1, D + 1), dtype=torch.int32, device=DEV)
+        kw = {f"norm_{k}": fff_lib.from_numpy(norm[k], DEV) for k in ("gamma", "beta") if k in norm}
+        y = fff_lib.forward(x, wi, wo, D, 1, mode="generic", y_dtype=TORCH_DT[yd], out="residual", norm="layernorm",
+                            norm_eps=1e-5, nodes_out=nodes, **kw)
+        torch.cuda.synchronize()
+        ref = oracle.block(L["x"], L["w_in"], L["w_out"], D, 1, norm=norm)
+        parity.assert_parity(ref["u"], L["w_in"], L["w_out"], D, 1, dict(ref, y=ref["fff"]), fff_lib.to_numpy(y),
+                             nodes.cpu().numpy(), tol=tol_for(wd, yd), base_dev=L["x"])
+    y0 = synth.make_x(411, B, H, yd)
+    got = run_fff(fff_lib, L, D, 1, yd, mode="generic", out="accumulate", y_init=y0)
+    ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
+    parity.assert_parity(L["x"], L["w_in"], L["w_out"], D, 1, ref, got["y"], got["nodes"], tol=tol_for(wd, yd), base_dev=y0)
