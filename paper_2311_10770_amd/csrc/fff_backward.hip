@@ -8,7 +8,7 @@
 //     dW_out[t,n] += a * dy_b,   dl = <dy_b, W_out[t,n]> act'(l),
 //     dW_in[t,n]  += dl * x_b,   dx_b += dl * W_in[t,n].
 //
-// 1. bwd_token_kernel (or bwd_generic_token_kernel): a group of lanes per
+// 1. bwd_token_kernel (bwd_wide_token_kernel, bwd_generic_token_kernel): a group of lanes per
 //    token, dy in registers; per level the two rows of the known path are
 //    gathered, da is reduced across the group, dx accumulates in registers;
 //    the pair (a, dl) of every visit is saved and the leaves are counted.
@@ -31,6 +31,7 @@
 #include "fff_common.hpp"
 #include "fff_device.hpp"
 #include "fff_internal.hpp"
+#include "fff_wide.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -122,6 +123,75 @@ __global__ __launch_bounds__(BLOCK) void bwd_token_kernel(BwdParams p) {
     }
 }
 
+// Any hidden size whose rows are whole 16-byte vectors (fff_wide.hpp): as bwd_token_kernel with a
+// run-time row length and the next level's two rows in flight (the path is known).  In place of the
+// wave per token and element per lane below: 61.5 -> 28.0 us at 3 trees of depth 6, hidden 300, 2003
+// tokens, fp32 (bound by the chain of 21 levels per token at two waves per SIMD).
+template <int LANES, int NV, bool WBF>
+__global__ __launch_bounds__(BWD_BLOCK) void bwd_wide_token_kernel(BwdParams p, int rowv) {
+    using S = Shape<LANES, NV, false, WBF>;
+    constexpr int WAVES = BWD_BLOCK / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sl = lane % LANES, sub = lane / LANES;
+    const int T = p.n_trees, D = p.depth;
+    const int64_t L = int64_t(1) << D;
+    const uint32_t rowb = uint32_t(rowv) * 16;
+    WideRows<LANES, NV> win, wout;
+    win.init(p.w_in, int64_t(T) * p.n_nodes * rowb, rowv, sl);
+    wout.init(p.w_out, int64_t(T) * p.n_nodes * rowb, rowv, sl);
+    const int64_t n_groups = (p.n_tokens + S::TPW - 1) / S::TPW;
+    for (int64_t g = int64_t(blockIdx.x) * WAVES + wave; g < n_groups; g += int64_t(gridDim.x) * WAVES) {
+        const int64_t slot = g * S::TPW + sub;
+        const bool valid = slot < p.n_tokens;
+        const int64_t tok = valid ? slot : p.n_tokens - 1;
+        XRegs<LANES, NV, false, WBF> gy;
+        wide_load_f32<LANES, NV, WBF>(gy.f, p.dy, p.dy_bf16, tok, rowv, sl);
+        float acc[S::E];
+#pragma unroll
+        for (int e = 0; e < S::E; ++e) acc[e] = 0.0f;
+        for (int t = 0; t < T; ++t) {
+            // an out-of-range leaf stands for the first one with zero weights; nothing of it is stored
+            const int32_t leaf = p.leaves[tok * T + t];
+            const bool ok = valid && leaf_ok(leaf, D);
+            const uint32_t leaf1 = uint32_t(ok ? leaf : int32_t(L - 1)) + 1;
+            if (sl == 0) {
+                if (ok && p.need_dw) atomicAdd(&p.counts[t * L + (int64_t(leaf1) - L)], 1);
+                if (valid && !ok && p.bad) atomicAdd(p.bad, 1);
+            }
+            const uint32_t tree = uint32_t(t) * uint32_t(p.n_nodes) * rowb;
+            const int64_t rec0 = (tok * T + t) * (D + 1);
+            uint4 ro[2][NV], ri[2][NV];
+            float lg[2];
+            auto load = [&](int l, int b) {
+                const uint32_t row = tree + ((leaf1 >> (D - l)) - 1) * rowb;
+                wout.load(row, ro[b]);
+                win.load(row, ri[b]);
+                lg[b] = p.logits[rec0 + l];
+            };
+            auto level = [&](int l, int b) {
+                const float logit = ok ? lg[b] : 0.0f;
+                const float da = group_sum<LANES>(gy.dot(ro[b]));
+                const float dl = ok ? da * activation_grad(logit, p.act) : 0.0f;
+                axpy<NV, WBF>(acc, dl, ri[b]);
+                if (ok && sl == 0 && p.need_dw) p.coef[rec0 + l] = make_float2(activation(logit, p.act), dl);
+            };
+            load(0, 0);
+            for (int l = 0;; l += 2) {
+                load(l + 1 <= D ? l + 1 : D, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                level(l, 0);
+                if (l + 1 > D) break;
+                load(l + 2 <= D ? l + 2 : D, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                level(l + 1, 1);
+                if (l + 2 > D) break;
+            }
+        }
+        if (valid && p.dx)
+            wide_store<LANES, NV, WBF>(p.dx, p.dx_bf16, p.accumulate ? p.dx : nullptr, p.dx_bf16, acc, tok, rowv, sl);
+    }
+}
+
 template <bool BF>
 __device__ __forceinline__ float load1(const void* base, int64_t i) {
     if constexpr (BF) return bf16_to_f32(reinterpret_cast<const uint16_t*>(base)[i]);
@@ -132,7 +202,7 @@ __device__ __forceinline__ float load1r(const void* base, bool bf, int64_t i) {
     return bf ? load1<true>(base, i) : load1<false>(base, i);
 }
 
-// Any hidden size: one wave per token; first the pairs of every visit (kept
+// Any other hidden size: one wave per token; first the pairs of every visit (kept
 // in LDS), then dx one 64-column block at a time.
 constexpr int BWD_GENERIC_MAX_PAIRS = 2048;
 
@@ -522,7 +592,8 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_piece_kernel(BwdParams p) {
         return w;
     };
 
-    for (int l0 = 0; l0 <= D; l0 += LV) {
+    {
+        const int l0 = int(blockIdx.y) * LV;  // this wave's levels
         int32_t cur[LV];    // node of the current run per level (wave-uniform)
         uint32_t head = 0;  // bit j: the current run of level l0+j began before this piece
         float ao[LV][4], ai[LV][4];
@@ -1472,6 +1543,26 @@ const BwdVariant kBwdVariants[] = {
     FFF_BWD(1024, false, 32, 8), FFF_BWD(4096, true, 64, 8), FFF_BWD(4096, false, 64, 16),
 };
 
+// The vector-row token kernel for p's width (kernel null where it does not apply).
+struct BwdWide {
+    const void* kernel = nullptr;
+    int rowv = 0, lanes = 0;
+};
+
+BwdWide bwd_wide(const BwdParams& p) {
+    BwdWide w;
+    w.rowv = wide_vecs(p.hidden, p.w_bf16, int64_t(p.n_trees) * p.n_nodes);
+    if (!w.rowv) return w;
+    auto fill = [&](auto lanes, auto nv, auto wbf) {
+        constexpr int LN = decltype(lanes)::value, NV = decltype(nv)::value;
+        w.lanes = LN;
+        w.kernel = reinterpret_cast<const void*>(&bwd_wide_token_kernel<LN, NV, decltype(wbf)::value>);
+    };
+    if (p.w_bf16) wide_class<true>(w.rowv, [&](auto l, auto n) { fill(l, n, std::true_type{}); });
+    else wide_class<false>(w.rowv, [&](auto l, auto n) { fill(l, n, std::false_type{}); });
+    return w;
+}
+
 int resident_blocks(const void* kernel, size_t lds) {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, BWD_BLOCK, lds) != hipSuccess || n < 1) n = 1;
@@ -1481,10 +1572,12 @@ int resident_blocks(const void* kernel, size_t lds) {
 }  // namespace
 
 int32_t bwd_piece(int64_t n_tokens, int32_t n_trees) {
-    // about 1024 pieces over all trees (x 3 column slices at hidden 768: three
-    // waves per SIMD), at least 64 positions (one perm load per lane)
+    // about 1024 pieces over all trees (x 3 column slices at hidden 768: three waves per SIMD), at
+    // least 16 positions: a wave takes its piece's tokens one after another (3 trees of depth 6,
+    // hidden 300, 2003 tokens: pieces of 64 positions, all levels in one wave, 84.8 us; of 16, a wave
+    // per six levels, 21.2, and 4 more in the fix-ups)
     const int64_t want = (n_tokens * n_trees + 1023) / 1024;
-    return int32_t(std::max<int64_t>(64, (want + 63) / 64 * 64));
+    return int32_t(std::max<int64_t>(16, (want + 15) / 16 * 16));
 }
 
 static int64_t bwd_pieces(int64_t n_tokens, int32_t piece) { return std::max<int64_t>(1, (n_tokens + piece - 1) / piece); }
@@ -1609,6 +1702,7 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
         return hipSuccess;
     }
     const int64_t cap = int64_t(dev.cu_count) * 8;
+    BwdWide wide = v ? BwdWide{} : bwd_wide(p);
     // bf16 weights, one tree, depth <= 15, hidden 128..1024: the fused leaf-tiled backward
     p.fused = p.need_dw && p.w_bf16 && p.n_trees == 1 && wtile_shape(p.depth, p.hidden) && p.hidden <= 1024;
     if (p.fused) {
@@ -1647,6 +1741,10 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
             k = v->token;
             const int64_t groups = (p.n_tokens + 64 / v->lanes - 1) / (64 / v->lanes);
             want = (groups + BWD_BLOCK / 64 - 1) / (BWD_BLOCK / 64);
+        } else if (wide.kernel) {
+            k = wide.kernel;
+            const int64_t per = BWD_BLOCK / wide.lanes;
+            want = (p.n_tokens + per - 1) / per;
         } else {
             k = p.w_bf16 ? reinterpret_cast<const void*>(&bwd_generic_token_kernel<true>)
                          : reinterpret_cast<const void*>(&bwd_generic_token_kernel<false>);
@@ -1655,7 +1753,8 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
         }
         const int64_t resident = int64_t(dev.cu_count) * resident_blocks(k, lds);
         const int grid = int(std::max<int64_t>(1, std::min(want, resident)));
-        const hipError_t e = hipLaunchKernel(k, dim3(grid), dim3(BWD_BLOCK), args, lds, stream);
+        void* targs[] = {&p, &wide.rowv};  // the second argument is the vector-row kernel's only
+        const hipError_t e = hipLaunchKernel(k, dim3(grid), dim3(BWD_BLOCK), targs, lds, stream);
         if (e != hipSuccess) return e;
     }
     if (!p.need_dw) return hipSuccess;
@@ -1678,8 +1777,8 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
     {
         const int64_t waves = int64_t(p.pieces) * slices * p.n_trees;
         const int64_t grid = (waves + BWD_BLOCK / 64 - 1) / (BWD_BLOCK / 64);
-        e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_piece_kernel), dim3(unsigned(grid)), dim3(BWD_BLOCK),
-                            args, 0, stream);
+        e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_piece_kernel),
+                            dim3(unsigned(grid), unsigned((p.depth + LV) / LV)), dim3(BWD_BLOCK), args, 0, stream);
         if (e != hipSuccess) return e;
     }
     {

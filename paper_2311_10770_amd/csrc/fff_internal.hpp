@@ -103,7 +103,7 @@ struct BwdParams {
     int32_t need_dw;         // dW_in or dW_out requested
 };
 
-// Sorted positions per piece of the backward's weight kernel (a multiple of 64).
+// Sorted positions per piece of the backward's weight kernel (a multiple of 16).
 int32_t bwd_piece(int64_t n_tokens, int32_t n_trees);
 // Workspace of the backward; the views are carved by bwd_workspace_views.
 size_t bwd_workspace_bytes(int64_t n_tokens, int32_t depth, int32_t n_trees, int32_t hidden);

@@ -113,7 +113,8 @@ auto wide_class(int rowv, F&& f) {
     if constexpr (!HEAVY)
         if (rowv <= 96) return f(integral_constant<int, 16>{}, integral_constant<int, 6>{});
     if (rowv <= 128) return f(integral_constant<int, 32>{}, integral_constant<int, 4>{});
-    if (rowv <= 192) return f(integral_constant<int, 32>{}, integral_constant<int, 6>{});
+    if constexpr (!HEAVY)
+        if (rowv <= 192) return f(integral_constant<int, 32>{}, integral_constant<int, 6>{});
     if (rowv <= 256) return f(integral_constant<int, 64>{}, integral_constant<int, 4>{});
     if (rowv <= 384) return f(integral_constant<int, 64>{}, integral_constant<int, 6>{});
     return f(integral_constant<int, 64>{}, integral_constant<int, 8>{});

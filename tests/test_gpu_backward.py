@@ -247,3 +247,39 @@ def test_fused_accumulate_dw_only_and_bad_leaves(fff_lib):
         g = got[k][keep] if k == "dx" else got[k]
         err = np.abs(g - ref[k]).max()
         assert err <= 1e-5 * np.abs(ref[k]).max(), (k, err)
+
+
+@pytest.mark.parametrize("xd,wd,H", [("f32", "f32", h) for h in (4, 132, 260, 300, 516, 772, 1028, 1540, 2044, 2052)] +
+                         [("bf16", "bf16", h) for h in (8, 264, 520, 1032, 1544, 2056, 4088, 4104)] +
+                         [("bf16", "f32", 300), ("f32", "bf16", 264)])
+def test_vector_row_widths(fff_lib, xd, wd, H):
+    """Widths without kernels of their own on both sides of every lane layout's capacity: bounds on
+    Gaussian inputs, and exact sums (accumulated onto integers) on small ones."""
+    L = synth.make_layer(340 + H, 333, H, 5, 2, xd, wd)
+    bounded_case(fff_lib, f"vectors {xd}/{wd} H={H}", L, 5, 2, synth.make_x(341, 333, H, xd))
+    B, D, T = 97, 6, 3
+    L = int_layer(342 + H, B, H, D, T, wd)
+    dy = synth.as_dtype(np.random.default_rng(2).integers(-3, 4, (B, H)).astype(np.float32), wd)
+    fwd = oracle.forward(L["x"], L["w_in"], L["w_out"], D, T, act="identity")
+    rng = np.random.default_rng(3)
+    init = {k: rng.integers(-9, 10, s).astype(np.float32) for k, s in
+            (("dx", (B, H)), ("dw_in", L["w_in"].shape), ("dw_out", L["w_out"].shape))}
+    got = run_bwd(fff_lib, L, D, T, dy, fwd["nodes"][:, :, D].astype(np.int32), fwd["logits"].astype(np.float32),
+                  act="identity", accumulate=True, init=init)
+    ref = oracle.backward(L["x"], L["w_in"], L["w_out"], D, T, dy, fwd["nodes"], act="identity")
+    for k in ("dx", "dw_in", "dw_out"):
+        assert np.array_equal(got[k].astype(np.float64), ref[k] + init[k]), k
+
+
+@pytest.mark.parametrize("B,D,T", [(15, 2, 1), (16, 2, 1), (17, 5, 1), (16384, 3, 1), (16400, 6, 2), (70000, 1, 1)])
+def test_weight_sum_pieces(fff_lib, B, D, T):
+    """The run sums in pieces (a width the leaf-tiled kernel does not take): fewer tokens than one
+    piece, exactly one, pieces of 16 positions up to the longest, one and two level passes."""
+    L = int_layer(350 + B, B, 20, D, T, "f32")
+    dy = np.random.default_rng(4).integers(-3, 4, (B, 20)).astype(np.float32)
+    fwd = oracle.forward(L["x"], L["w_in"], L["w_out"], D, T, act="identity")
+    got = run_bwd(fff_lib, L, D, T, dy, fwd["nodes"][:, :, D].astype(np.int32), fwd["logits"].astype(np.float32),
+                  act="identity")
+    ref = oracle.backward(L["x"], L["w_in"], L["w_out"], D, T, dy, fwd["nodes"], act="identity")
+    for k in ("dx", "dw_in", "dw_out"):
+        assert np.array_equal(got[k].astype(np.float64), ref[k]), k
