@@ -30,6 +30,7 @@
 //    root rows alone took over a thousand of them per element.)
 #include "fff_common.hpp"
 #include "fff_device.hpp"
+#include "fff_gemm.hpp"
 #include "fff_internal.hpp"
 #include "fff_wide.hpp"
 
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_place_kernel(BwdParams p) {
         if (!leaf_ok(leaf, D)) {
             if (p.fused) {  // no token kernel ran: count the pair and give the token a zero dx row
                 if (p.bad) atomicAdd(p.bad, 1);
-                if (p.dx && !p.accumulate) {
+                if (p.dx && !p.accumulate && t == 0) {  // the first tree stores dx, the others add
                     for (int64_t c = 0; c < p.hidden; ++c) {
                         if (p.dx_bf16) reinterpret_cast<uint16_t*>(p.dx)[b * p.hidden + c] = 0;
                         else reinterpret_cast<float*>(p.dx)[b * p.hidden + c] = 0.0f;
@@ -510,6 +511,13 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_place_kernel(BwdParams p) {
         const int64_t bin = int64_t(leaf) - (L - 1);
         const int64_t pos = p.hist[(int64_t(t) * p.chunks + b / p.chunk) * L + bin] + p.rank[int64_t(t) * p.n_tokens + b];
         p.perm[int64_t(t) * p.n_tokens + pos] = int32_t(b);
+    }
+    if (p.fused16) {  // act(l) and act'(l) of every visit
+        const int64_t m = n * (D + 1);
+        for (int64_t i = int64_t(blockIdx.x) * BWD_BLOCK + threadIdx.x; i < m; i += int64_t(gridDim.x) * BWD_BLOCK) {
+            const float l = p.logits[i];
+            p.coef[i] = make_float2(activation(l, p.act), activation_grad(l, p.act));
+        }
     }
 }
 
@@ -1458,6 +1466,309 @@ __global__ __launch_bounds__(64 * FUSED_WAVES_MAX) void bwd_fused_kernel(BwdPara
     }
 }
 
+// ---------------------------------------------------------------------------
+// 1''. the same with bf16 x and dy (hidden 256..768)
+// ---------------------------------------------------------------------------
+//
+// As bwd_fused_kernel, one wave per 64-column group: a wave's dy and x rows of the next tile are
+// written straight to LDS (lds_dma16) while a tile runs, rows past the tile's count taken from a
+// row of zeros, and both the da operand (row reads) and the operands of the dW sums (transposing
+// reads) come from there, so that no load of a tile waits in registers; act(l) and act'(l) are
+// computed by bwd_place_kernel.  Twelve waves of at most 168 registers, three per SIMD (hidden 768).
+// Against bwd_fused_kernel's six waves of 128 columns, which held the tiles in registers (two waves on
+// two of the SIMDs, one on the others; 6 us per tile of sixteen tokens, most of it waiting between
+// the two barriers of a tile): 134 -> 101 us at 65536 tokens, depth 11, hidden 768, the backward 158 ->
+// 128; depth 7, 206 -> 140; depth 5, 16384 tokens, 182 -> 121.  Of the 101 us the dx stores take 18,
+// the dW products 9, adding the partial da 8, the partial rows above the subtrees 4.  Slower forms:
+// sixteen waves at hidden 1024 (128 registers, 41 spilled: 238 against 178 us, so the widths above 768
+// stay with bwd_fused_kernel, as does 128, which has too few waves for the tile's 256 entries); the
+// next leaf's W rows in flight during a leaf's last tile (47 spills) or while its dW rows are stored (12:
+// 124 us); dW columns transposed across lanes for 16-byte stores (143 us per backward); 256 subtrees of
+// eight leaves in place of 512 of four (125 us: no second round to even out the leaves' sizes).
+constexpr int F16_COLS = 64, F16_WAVES_MAX = 12;
+constexpr int F16_TOK = 1024;  // sorted token ids staged in LDS at a time
+typedef short f16_s4 __attribute__((ext_vector_type(4)));
+
+// The order of the eight 16-byte vectors of LDS row r: vector c at c ^ key, so that the four rows of
+// a transposing read, and the eight rows of a row read, fall on different banks.
+__device__ __forceinline__ int f16_key(int r) { return ((r & 3) * 2) ^ ((r >> 2) & 1) ^ (((r >> 3) & 1) * 4); }
+
+// MFMA operand of rows row0 .. row0 + 7 (K) of a [16][64] bf16 tile at columns 16 j + n: a transposing
+// read hands lane n of sixteen column n of the 4 x 16 block their addresses cover (lane i: row i / 4,
+// columns 4 (i % 4) .. +3; checked on the GPU), so two reads give rows 0..3 and 4..7.
+__device__ __forceinline__ bf16x8_t f16_tr(const unsigned char* tile, int row0, int j, int n) {
+    typedef __attribute__((address_space(3))) f16_s4* lds_s4;
+    uint2 u[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = row0 + 4 * h + (n >> 2), c = 2 * j + ((n & 3) >> 1);
+        u[h] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                             (lds_s4)(tile + r * 128 + ((c ^ f16_key(r)) * 16) + (n & 1) * 8)));
+    }
+    return __builtin_bit_cast(bf16x8_t, make_uint4(u[0].x, u[0].y, u[1].x, u[1].y));
+}
+
+__global__ __launch_bounds__(64 * F16_WAVES_MAX) void bwd_fused16_kernel(BwdParams p, int sub, int tree, int dx_add) {
+    constexpr int TILE = 16 * 128, WBUF = 4 * TILE;  // a wave's tiles: two buffers of dy and x
+    extern __shared__ __align__(16) unsigned char f16_lds[];  // [waves][2][dy, x][16][64] bf16
+    __shared__ float red[F16_WAVES_MAX][16][17];                // per-wave partial da [token][level]
+    // a and dl as three bf16 parts (hi + mid + lo = the fp32 value to fp32 precision): dl token-major for
+    // dx, both level-major for the dW sums
+    __shared__ __align__(16) uint16_t s_dlQ[3][16][16], s_aP[3][16][16], s_dlP[3][16][16];
+    __shared__ int32_t s_cnt[1 << WT_MAX_SUB], s_next[1 << WT_MAX_SUB];  // tokens of a leaf; the next leaf with any
+    __shared__ int32_t s_tok[F16_TOK];
+    const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, q = lane >> 4, h = q & 1, part = q >> 1;
+    const int D = p.depth, T = p.n_trees, t = tree + int(blockIdx.y);
+    const int64_t L = int64_t(1) << D, H = p.hidden, N = p.n_nodes;
+    const int k = D - sub, nleaf = 1 << sub;
+    const int64_t st = blockIdx.x, leaf0 = st << sub;
+    const int32_t* const cnt = p.counts + t * L;
+    const int32_t* const end = p.offs + t * L;  // after the placement: one past each leaf's last position
+    const int32_t* const perm = p.perm + int64_t(t) * p.n_tokens;
+    const bool add = p.accumulate != 0;
+    const int64_t col = int64_t(wave) * F16_COLS;
+    const uint16_t* const dy16 = static_cast<const uint16_t*>(p.dy) + col;
+    const uint16_t* const x16 = static_cast<const uint16_t*>(p.x) + col;
+    const uint16_t* const wout16 = static_cast<const uint16_t*>(p.w_out) + int64_t(t) * N * H + col;
+    const uint16_t* const win16 = static_cast<const uint16_t*>(p.w_in) + int64_t(t) * N * H + col;
+    float* const dwo = p.dw_out ? p.dw_out + int64_t(t) * N * H + col : nullptr;
+    float* const dwi = p.dw_in ? p.dw_in + int64_t(t) * N * H + col : nullptr;
+    unsigned char* const wbuf = f16_lds + wave * WBUF;
+    const uint32_t wlds = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char*)wbuf));
+
+    for (int i = tid; i < nleaf; i += blockDim.x) s_cnt[i] = cnt[leaf0 + i];
+    const int64_t first = int64_t(end[leaf0]) - cnt[leaf0], last = end[leaf0 + nleaf - 1];
+    int64_t win0 = first;  // s_tok holds positions win0 .. win0 + F16_TOK - 1 (clipped to the subtree)
+    auto stage = [&]() {
+        for (int64_t i = tid; i < F16_TOK && win0 + i < last; i += blockDim.x) s_tok[i] = perm[win0 + i];
+    };
+    stage();
+    __syncthreads();
+    if (tid < nleaf) {
+        int j = tid + 1;
+        while (j < nleaf && s_cnt[j] == 0) ++j;
+        s_next[tid] = j;
+    }
+    __syncthreads();
+
+    // The W rows of a leaf's path.  wo, the da operand: lane (level n, q) holds W_out[node(n)][32 s + 8 q
+    // .. +7]; wi, for dx: columns 4n .. 4n+3 of the W_in rows of levels 8h .. 8h+7.
+    struct Rows {
+        uint4 wo[2];
+        uint2 wi[8];
+    };
+    auto load_rows = [&](int64_t leaf, Rows& r) {
+        const uint32_t leaf1 = uint32_t(leaf + L);
+        const int lv = n <= D ? n : D;  // levels past D: any row (their results are not used)
+        const int64_t node = int64_t(leaf1 >> (D - lv)) - 1;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) r.wo[s] = *reinterpret_cast<const uint4*>(wout16 + node * H + 32 * s + 8 * q);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int l = 8 * h + i <= D ? 8 * h + i : D;
+            r.wi[i] = *reinterpret_cast<const uint2*>(win16 + (int64_t(leaf1 >> (D - l)) - 1) * H + 4 * n);
+        }
+    };
+    // A tile's (act, act') of entry (token tid / 16, level tid % 16), for the first four waves.
+    const int at = tid >> 4, alv = tid & 15;
+    auto load_cf = [&](int64_t P, int m) {
+        float2 c = make_float2(0.f, 0.f);
+        if (tid < 256 && at < m && alv <= D) c = p.coef[(int64_t(s_tok[P + at - win0]) * T + t) * (D + 1) + alv];
+        return c;
+    };
+    // The dy and x rows of positions P .. P + m - 1 into buffer b; zeros for the rest of the tile.
+    auto issue = [&](int64_t P, int m, int b) {
+        const char* const zeros = reinterpret_cast<const char*>(g_norm_zeros);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 8 * i + (lane >> 3), c = ((lane & 7) ^ f16_key(r)) * 16;
+            const int64_t row = r < m ? int64_t(s_tok[P + r - win0]) * H : 0;
+            lds_dma16(r < m ? reinterpret_cast<const char*>(dy16 + row) + c : zeros + c, wlds + b * 2 * TILE + i * 1024);
+            lds_dma16(r < m ? reinterpret_cast<const char*>(x16 + row) + c : zeros + c, wlds + b * 2 * TILE + TILE + i * 1024);
+        }
+    };
+
+    tile_v4f ao[4], ai[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ao[j] = ai[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+    auto put_dw = [&](float* row, const tile_v4f (&acc)[4], int r, bool add_to) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float* const d = row + 16 * j + n;
+            *d = add_to ? *d + acc[j][r] : acc[j][r];
+        }
+    };
+
+    int jf = 0;  // first leaf with tokens
+    if (s_cnt[0] == 0) jf = s_next[0];
+    float2 cf_n = make_float2(0.f, 0.f);
+    if (jf < nleaf) {  // workgroup-uniform
+        const int m = s_cnt[jf] < 16 ? s_cnt[jf] : 16;
+        cf_n = load_cf(first, m);
+        issue(first, m, 0);
+        wait_vmem<0>();
+    }
+    int64_t pos0 = first;
+    int buf = 0;
+    for (int jl = 0; jl < nleaf; ++jl) {
+        const int64_t leaf = leaf0 + jl;
+        const int32_t c = s_cnt[jl];
+        if (c > 0) {  // workgroup-uniform
+            Rows rows;
+            load_rows(leaf, rows);
+            // dx B operand: bj[j] = column 4n + j of the W_in rows of levels 8h .. 8h+7
+            bf16x8_t bj[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t w4[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t lo = j / 2 ? rows.wi[2 * i].y : rows.wi[2 * i].x;
+                    const uint32_t hi = j / 2 ? rows.wi[2 * i + 1].y : rows.wi[2 * i + 1].x;
+                    w4[i] = (j & 1) ? (lo >> 16) | (hi & 0xffff0000u) : (lo & 0xffffu) | (hi << 16);
+                }
+                bj[j] = __builtin_bit_cast(bf16x8_t, make_uint4(w4[0], w4[1], w4[2], w4[3]));
+            }
+            const int jn = s_next[jl];
+            for (int32_t t0 = 0; t0 < c; t0 += 16, buf ^= 1) {
+                const int m = c - t0 < 16 ? c - t0 : 16;
+                const int64_t P = pos0 + t0;
+                // The tile's rows are the oldest of this wave's memory operations but for the dx stores
+                // of the tile before, at least four (operations retire in order).
+                wait_vmem<4>();
+                asm volatile("" ::: "memory");
+                float2 cf = cf_n;
+                asm volatile("" : "+v"(cf.x), "+v"(cf.y));  // waited for here, before the next tile's loads
+                const unsigned char* const dyt = wbuf + buf * 2 * TILE;
+                const unsigned char* const xt = dyt + TILE;
+                int32_t rtok[4];  // tokens of this lane's dx rows, -1 for none
+#pragma unroll
+                for (int r = 0; r < 4; ++r) rtok[r] = 4 * q + r < m ? s_tok[P + 4 * q + r - win0] : -1;
+                // 1. partial da over this wave's columns: lane (token n, q) supplies dy, (level n, q) gets
+                //    tokens 4q + r
+                tile_v4f da = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    da = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(dyt + n * 128 + (((4 * s + q) ^ f16_key(n)) * 16))),
+                        __builtin_bit_cast(bf16x8_t, rows.wo[s]), da, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[wave][4 * q + r][n] = da[r];
+                // the next tile (the rest of this leaf, or the next leaf with tokens), if any
+                const bool same = t0 + 16 < c;
+                const int jx = same ? jl : jn;
+                if (jx < nleaf) {  // workgroup-uniform
+                    const int64_t Pn = same ? P + 16 : pos0 + c;
+                    const int left = same ? c - t0 - 16 : s_cnt[jx], mn = left < 16 ? left : 16;
+                    if (Pn + mn > win0 + F16_TOK) {
+                        __syncthreads();  // every wave has read this tile's ids
+                        win0 = Pn;
+                        stage();
+                        __syncthreads();
+                    }
+                    cf_n = load_cf(Pn, mn);
+                    issue(Pn, mn, buf ^ 1);
+                }
+                __syncthreads();
+                // 2. a and dl of the tile's (token, level) pairs, the partials added in wave order
+                if (wave < 4) {
+                    float d = 0.0f;
+                    for (int w = 0; w < waves; ++w) d += red[w][at][alv];
+                    const float dl = at < m && alv <= D ? d * cf.y : 0.0f;  // cf is zero where absent
+                    uint16_t dp[3], ap[3];
+                    split3(dl, dp);
+                    split3(cf.x, ap);
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) {
+                        s_dlQ[r][at][alv] = dp[r];
+                        s_dlP[r][alv][at] = dp[r];
+                        s_aP[r][alv][at] = ap[r];
+                    }
+                }
+                __syncthreads();
+                // 3. dx rows: A = parts of dl (token n, levels 8h .. 8h+7), hi and mid, then lo and zero
+                if (p.dx) {  // uniform
+                    const uint4 z4 = make_uint4(0u, 0u, 0u, 0u);
+                    const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, lds_u4(&s_dlQ[part][n][8 * h]));
+                    const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, part == 0 ? lds_u4(&s_dlQ[2][n][8 * h]) : z4);
+                    tile_v4f acc[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bj[j], tile_v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bj[j], acc[j], 0, 0, 0);
+                    }
+                    // lane (n, q): tokens 4q + r, columns 4n .. 4n+3; absent rows go to a junk area, so that
+                    // every tile issues the same stores
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool real = rtok[r] >= 0;
+                        float4 v = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+                        const int64_t e = int64_t(real ? rtok[r] : 0) * H + col + 4 * n;
+                        char* const jk = p.junk + lane * 32;
+                        if (p.dx_bf16) {
+                            uint2* const d = reinterpret_cast<uint2*>(real ? reinterpret_cast<char*>(static_cast<uint16_t*>(p.dx) + e) : jk);
+                            if (dx_add) {
+                                const uint2 o = *d;
+                                v.x += bf16_lo(o.x); v.y += bf16_hi(o.x); v.z += bf16_lo(o.y); v.w += bf16_hi(o.y);
+                            }
+                            *d = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+                        } else {
+                            float4* const d = reinterpret_cast<float4*>(real ? reinterpret_cast<char*>(static_cast<float*>(p.dx) + e) : jk);
+                            if (dx_add) {
+                                const float4 o = *d;
+                                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+                            }
+                            *d = v;
+                        }
+                    }
+                } else {
+                    wait_vmem<0>();  // no stores behind the next tile's rows
+                }
+                // 4. dW sums, K the tile's tokens: the hi and mid parts of a (dl) in one product and the lo
+                //    part and zero in a second, every product exact.  Lane (n, q): levels 4q + r, column 16j + n
+                const uint4 z4 = make_uint4(0u, 0u, 0u, 0u);
+                const bf16x8_t aa1 = __builtin_bit_cast(bf16x8_t, lds_u4(&s_aP[part][n][8 * h]));
+                const bf16x8_t aa2 = __builtin_bit_cast(bf16x8_t, part == 0 ? lds_u4(&s_aP[2][n][8 * h]) : z4);
+                const bf16x8_t ad1 = __builtin_bit_cast(bf16x8_t, lds_u4(&s_dlP[part][n][8 * h]));
+                const bf16x8_t ad2 = __builtin_bit_cast(bf16x8_t, part == 0 ? lds_u4(&s_dlP[2][n][8 * h]) : z4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bf16x8_t bd = f16_tr(dyt, 8 * h, j, n), bx = f16_tr(xt, 8 * h, j, n);
+                    ao[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aa1, bd, ao[j], 0, 0, 0);
+                    ao[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aa2, bd, ao[j], 0, 0, 0);
+                    ai[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ad1, bx, ai[j], 0, 0, 0);
+                    ai[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ad2, bx, ai[j], 0, 0, 0);
+                }
+            }
+        }
+        pos0 += c;
+        // rows this leaf completes (levels lv >= k whose node's last leaf this is)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int lv = 4 * q + r;
+            if (lv <= D && lv >= k && ((leaf + 1) & ((int64_t(1) << (D - lv)) - 1)) == 0) {
+                const int64_t node = ((leaf + L) >> (D - lv)) - 1;
+                if (dwo) put_dw(dwo + node * H, ao, r, add);
+                if (dwi) put_dw(dwi + node * H, ai, r, add);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ao[j][r] = ai[j][r] = 0.0f;
+            }
+        }
+    }
+    // levels above the subtree root: this subtree's sums for the fix-up
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int lv = 4 * q + r;
+        if (lv < k) {
+            float* const dst = p.part + ((((int64_t(t) << k) + st) * k + lv) * 2) * H + col;
+            put_dw(dst, ao, r, false);
+            put_dw(dst + H, ai, r, false);
+        }
+    }
+}
+
 // Rows of the levels above the subtrees (lv < k): node u at level lv sums the
 // part[] of its 2^(k-lv) subtrees.  One block per (tree, level, matrix,
 // 64-column slice); thread (column quad c, group g) owns four columns and
@@ -1685,8 +1996,8 @@ static hipError_t launch_sort(BwdParams& p, bool count_leaves, const int64_t cap
     e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_base_kernel),
                         dim3(unsigned((bins + BWD_BLOCK / 64 - 1) / (BWD_BLOCK / 64))), dim3(BWD_BLOCK), bargs, 0, stream);
     if (e != hipSuccess) return e;
-    const int64_t n = p.n_tokens * p.n_trees;
-    const int grid = int(std::max<int64_t>(1, std::min<int64_t>((n + BWD_BLOCK - 1) / BWD_BLOCK, cap)));
+    const int64_t n = p.n_tokens * p.n_trees, work = p.fused16 ? n * (p.depth + 1) : n;
+    const int grid = int(std::max<int64_t>(1, std::min<int64_t>((work + BWD_BLOCK - 1) / BWD_BLOCK, cap)));
     return hipLaunchKernel(reinterpret_cast<const void*>(&bwd_place_kernel), dim3(grid), dim3(BWD_BLOCK), args, 0,
                            stream);
 }
@@ -1706,10 +2017,20 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
     // bf16 weights, one tree, depth <= 15, hidden 128..1024: the fused leaf-tiled backward
     p.fused = p.need_dw && p.w_bf16 && p.n_trees == 1 && wtile_shape(p.depth, p.hidden) && p.hidden <= 1024;
     if (p.fused) {
+        p.fused16 = p.x_bf16 && p.dy_bf16 && p.hidden >= 4 * F16_COLS && p.hidden <= F16_COLS * F16_WAVES_MAX;
         hipError_t e = launch_sort(p, true, cap, stream);
         if (e != hipSuccess) return e;
         const int k = wtile_k(p.depth);
         int sub = p.depth - k;
+        if (p.fused16) {
+            const int waves = p.hidden / F16_COLS;
+            int tree = 0, dx_add = p.accumulate;
+            void* fargs[] = {&p, &sub, &tree, &dx_add};
+            e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_fused16_kernel), dim3(unsigned(int64_t(1) << k)), dim3(64 * waves), fargs,
+                                size_t(waves) * 4 * 16 * 2 * F16_COLS, stream);
+            if (e != hipSuccess) return e;
+            return launch_wsum(p, k, stream);
+        }
         const void* kern = p.x_bf16 ? (p.dy_bf16 ? reinterpret_cast<const void*>(&bwd_fused_kernel<true, true>)
                                                  : reinterpret_cast<const void*>(&bwd_fused_kernel<true, false>))
                                     : (p.dy_bf16 ? reinterpret_cast<const void*>(&bwd_fused_kernel<false, true>)

@@ -283,3 +283,47 @@ def test_weight_sum_pieces(fff_lib, B, D, T):
     ref = oracle.backward(L["x"], L["w_in"], L["w_out"], D, T, dy, fwd["nodes"], act="identity")
     for k in ("dx", "dw_in", "dw_out"):
         assert np.array_equal(got[k].astype(np.float64), ref[k]), k
+
+
+@pytest.mark.parametrize("H", [128, 256, 640, 768, 896])
+@pytest.mark.parametrize("B,D", [(1, 6), (33, 0), (700, 3), (2500, 5), (600, 12), (300, 15)])
+def test_fused_bf16_widths(fff_lib, H, B, D):
+    """The fused backward with bf16 x, W and dy on both sides of the 64-column kernel's widths (256 to
+    768): exact integer sums, empty leaves, one token, more tokens in a subtree than the ids staged at a
+    time, the deepest tree; dx, dW_in and dW_out together and one at a time."""
+    L = int_layer(360 + H + B, B, H, D, 1, "bf16")
+    dy = synth.as_dtype(np.random.default_rng(5).integers(-3, 4, (B, H)).astype(np.float32), "bf16")
+    fwd = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1, act="identity")
+    leaves, logits = fwd["nodes"][:, :, D].astype(np.int32), fwd["logits"].astype(np.float32)
+    got = run_bwd(fff_lib, L, D, 1, dy, leaves, logits, act="identity")
+    ref = oracle.backward(L["x"], L["w_in"], L["w_out"], D, 1, dy, fwd["nodes"], act="identity")
+    for k in ("dx", "dw_in", "dw_out"):
+        assert np.array_equal(got[k].astype(np.float64), ref[k]), k
+    for k in ("dw_in", "dw_out"):
+        one = fff_lib.backward(dev(fff_lib, L["x"]), dev(fff_lib, L["w_in"]), dev(fff_lib, L["w_out"]), D, 1,
+                               dev(fff_lib, dy), dev(fff_lib, leaves), dev(fff_lib, logits), act="identity", want=(k,))
+        assert np.array_equal(fff_lib.to_numpy(one[("dx", "dw_in", "dw_out").index(k)]), got[k]), k
+    rng = np.random.default_rng(6)
+    init = {k: rng.integers(-9, 10, s).astype(np.float32) for k, s in
+            (("dx", (B, H)), ("dw_in", L["w_in"].shape), ("dw_out", L["w_out"].shape))}
+    acc = run_bwd(fff_lib, L, D, 1, dy, leaves, logits, act="identity", accumulate=True, init=init)
+    for k in ("dx", "dw_in", "dw_out"):
+        assert np.array_equal(acc[k].astype(np.float64), ref[k] + init[k]), k
+
+
+def test_fused_bf16_nan_stays_with_its_token(fff_lib):
+    """A nan in one token's x (dy) reaches that token's dx and its own path's dW rows only."""
+    B, H, D = 900, 768, 5
+    L = synth.make_layer(370, B, H, D, 1, "bf16", "bf16")
+    dy = synth.make_x(371, B, H, "bf16")
+    fwd = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
+    leaves, logits = fwd["nodes"][:, :, D].astype(np.int32), fwd["logits"].astype(np.float32)
+    L["x"] = L["x"].copy()
+    L["x"][7] = 0x7FC0
+    dy[7] = 0x7FC0
+    got = run_bwd(fff_lib, L, D, 1, dy, leaves, logits)
+    path = set(fwd["nodes"][7, 0].tolist())
+    other = [n for n in range(63) if n not in path]
+    assert np.isnan(got["dx"][7]).all() and np.isfinite(np.delete(got["dx"], 7, axis=0)).all()
+    for k in ("dw_in", "dw_out"):
+        assert np.isnan(got[k][0, sorted(path)]).all() and np.isfinite(got[k][0, other]).all(), k
