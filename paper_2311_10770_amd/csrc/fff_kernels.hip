@@ -413,74 +413,51 @@ enum { TSRC_NONE = 0, TSRC_F32 = 1, TSRC_BF16 = 2 };
 // empty rows then lies past every block).
 static int64_t tile_chunk_tokens(int64_t hidden) { return ((int64_t(1) << 31) - 1) / (4 * hidden); }
 
-// Eight consecutive output columns of one token: add the source and store,
-// through buffer resources over the source and destination rows.  An offset
-// past the resource's size (TILE_NO_ROW) makes the hardware drop the store and
-// read zeros, without a memory access.
+// NB (four or eight) consecutive columns of a source row, and of an output row that is stored with the
+// source added, through buffer resources over the rows.  An offset past the resource's size
+// (TILE_NO_ROW) makes the hardware drop the store and read zeros, without a memory access.
 typedef uint32_t tile_u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t tile_u2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t TILE_NO_ROW = 0x80000000u;
 
-template <int SRC, bool DBF>
-__device__ __forceinline__ void tile_store8_buf(__amdgpu_buffer_rsrc_t rs, uint32_t os, __amdgpu_buffer_rsrc_t rd,
-                                                uint32_t od, const float* v8) {
-    float v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = v8[i];
+template <int SRC, int NB>
+struct TileSrc {
+    tile_u4 v[SRC == TSRC_F32 ? NB / 4 : 1];
+};
+
+template <int SRC, int NB>
+__device__ __forceinline__ void tile_load_src(TileSrc<SRC, NB>& s, __amdgpu_buffer_rsrc_t rs, uint32_t os) {
     if constexpr (SRC == TSRC_F32) {
-        const tile_u4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, int(os), 0, 0);
-        const tile_u4 b = __builtin_amdgcn_raw_buffer_load_b128(rs, int(os + 16), 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t ai = a[i], bi = b[i];  // scalar copies: this compiler bit-casts a vector element as element 0
-            v[i] += __builtin_bit_cast(float, ai);
-            v[4 + i] += __builtin_bit_cast(float, bi);
-        }
+        for (int i = 0; i < NB / 4; ++i) s.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, int(os + 16 * i), 0, 0);
+    } else if constexpr (SRC == TSRC_BF16 && NB == 8) {
+        s.v[0] = __builtin_amdgcn_raw_buffer_load_b128(rs, int(os), 0, 0);
     } else if constexpr (SRC == TSRC_BF16) {
-        const tile_u4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, int(os), 0, 0);
+        const tile_u2 u = __builtin_amdgcn_raw_buffer_load_b64(rs, int(os), 0, 0);
+        s.v[0] = tile_u4{u[0], u[1], 0u, 0u};
+    }
+}
+
+template <int SRC, bool DBF, int NB>
+__device__ __forceinline__ void tile_store_buf(const TileSrc<SRC, NB>& s, __amdgpu_buffer_rsrc_t rd, uint32_t od,
+                                               const float* vin) {
+    float v[NB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] += bf16_lo(a[i]);
-            v[2 * i + 1] += bf16_hi(a[i]);
+    for (int i = 0; i < NB; ++i) {
+        v[i] = vin[i];
+        if constexpr (SRC == TSRC_F32) {
+            const uint32_t u = s.v[i / 4][i % 4];  // a scalar copy: this compiler bit-casts a vector element as element 0
+            v[i] += __builtin_bit_cast(float, u);
+        } else if constexpr (SRC == TSRC_BF16) {
+            v[i] += (i & 1) ? bf16_hi(s.v[0][i / 2]) : bf16_lo(s.v[0][i / 2]);
         }
     }
-    if constexpr (DBF) {
+    if constexpr (DBF && NB == 8) {
         const tile_u4 d = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
                            pack_bf16x2(v[6], v[7])};
         __builtin_amdgcn_raw_buffer_store_b128(d, rd, int(od), 0, 0);
     } else {
-        const tile_u4 d0 = {__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
-                            __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])};
-        const tile_u4 d1 = {__builtin_bit_cast(uint32_t, v[4]), __builtin_bit_cast(uint32_t, v[5]),
-                            __builtin_bit_cast(uint32_t, v[6]), __builtin_bit_cast(uint32_t, v[7])};
-        __builtin_amdgcn_raw_buffer_store_b128(d0, rd, int(od), 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(d1, rd, int(od + 16), 0, 0);
-    }
-}
-
-// The same for four consecutive columns.
-template <int SRC, bool DBF>
-__device__ __forceinline__ void tile_store4_buf(__amdgpu_buffer_rsrc_t rs, uint32_t os, __amdgpu_buffer_rsrc_t rd,
-                                                uint32_t od, const float* v4) {
-    float v[4] = {v4[0], v4[1], v4[2], v4[3]};
-    if constexpr (SRC == TSRC_F32) {
-        const tile_u4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, int(os), 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t ai = a[i];  // a scalar copy: this compiler bit-casts a vector element as element 0
-            v[i] += __builtin_bit_cast(float, ai);
-        }
-    } else if constexpr (SRC == TSRC_BF16) {
-        const tile_u2 a = __builtin_amdgcn_raw_buffer_load_b64(rs, int(os), 0, 0);
-        v[0] += bf16_lo(a[0]);
-        v[1] += bf16_hi(a[0]);
-        v[2] += bf16_lo(a[1]);
-        v[3] += bf16_hi(a[1]);
-    }
-    if constexpr (DBF) {
-        const tile_u2 d = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        __builtin_amdgcn_raw_buffer_store_b64(d, rd, int(od), 0, 0);
-    } else {
+        static_assert(!DBF && NB == 4, "bf16 rows eight columns at a time, fp32 rows four");
         const tile_u4 d = {__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
                            __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])};
         __builtin_amdgcn_raw_buffer_store_b128(d, rd, int(od), 0, 0);
@@ -620,8 +597,6 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
     // clamped; values past the count or past D are replaced by 0 where used), so
     // each path through a tile issues the same memory operations.
 
-    // stores of one tile's outputs: lane (n, kq) holds tokens 4 kq + r of the
-    // tile, whose ids come from the lanes that loaded them
     // Column layout in a 128-column group g.  With an fp32 destination (HALVES) MFMA column n of
     // block j is output column 128 g + 64 (j/4) + 4n + j%4, and the two halves (blocks 0..3, then
     // 4..7) are computed and stored in turn, so only four accumulators are live (fp32 weights: 74
@@ -629,20 +604,93 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
     // at once, one 16-byte store per row (measured faster there).
     constexpr bool HALVES = !DBF;
     constexpr int NB = HALVES ? 4 : 8;  // blocks per store
-    auto store_tile = [&](int32_t tok_a, const tile_v4f* acc, int64_t col) {
+    // A tile's result rows: lane (n, kq) holds tokens 4 kq + r of the tile, whose ids come from the lanes
+    // that loaded them (-1 past the count).
+    struct Rows {
+        int32_t tok[4];
+    };
+    auto rows_of = [&](int32_t tok_a) {
+        Rows w;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int32_t tok = __shfl(tok_a, 4 * kq + r, 64);
-            const int64_t e = int64_t(tok) * H + col;
-            float v[NB];
+        for (int r = 0; r < 4; ++r) w.tok[r] = __shfl(tok_a, 4 * kq + r, 64);
+        return w;
+    };
+    struct Src {
+        TileSrc<SRC, NB> r[4];
+    };
+    auto load_src = [&](const Rows& w, int64_t col, Src& sv) {
+        if constexpr (SRC != TSRC_NONE) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) v[j] = acc[j][r];
-            const uint32_t od = tok >= 0 ? uint32_t(e * DSZ) : TILE_NO_ROW;
-            const uint32_t os = tok >= 0 ? uint32_t(e * SSZ) : TILE_NO_ROW;
-            if constexpr (HALVES)
-                tile_store4_buf<SRC, DBF>(rsrc, os, rdst, od, v);
-            else
-                tile_store8_buf<SRC, DBF>(rsrc, os, rdst, od, v);
+            for (int r = 0; r < 4; ++r)
+                tile_load_src<SRC, NB>(sv.r[r], rsrc, w.tok[r] >= 0 ? uint32_t((int64_t(w.tok[r]) * H + col) * SSZ) : TILE_NO_ROW);
+        }
+    };
+    auto store_row = [&](int r, int32_t tok, const tile_v4f* acc, int64_t col, const Src& sv) {
+        float v[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) v[j] = acc[j][r];
+        tile_store_buf<SRC, DBF, NB>(sv.r[r], rdst, tok >= 0 ? uint32_t((int64_t(tok) * H + col) * DSZ) : TILE_NO_ROW, v);
+    };
+    auto store_tile = [&](const Rows& w, const tile_v4f* acc, int64_t col, const Src& sv) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) store_row(r, w.tok[r], acc, col, sv);
+    };
+    // The tiles of a column group, two operand sets in turn: the next tile's loads are in flight while
+    // one runs, and no register copy makes the wait early.  load(t0, raw) fetches a tile's operands,
+    // prepare(in, raw) makes them the A operand, product(c, a, acc) forms half c (or all) of the result.
+    // AHEAD: the source rows of the next half (or tile) are loaded before this one's stores: memory
+    // operations retire in order, and a load behind the stores would be waited for with them (the later
+    // trees of a 4x9 layer, fp32, 16384 tokens: 27.2 -> 23.0 us a tree; residual of fp32 x with bf16
+    // weights, depth 11, 65536 tokens: 181 -> 159 us).  Not for leaf pairs with a bf16 destination,
+    // mostly one tile each: the registers cost a wave per SIMD (depth 13, 8192 tokens 52 -> 58 us).
+    constexpr bool AHEAD = SRC != TSRC_NONE && !(PAIR && DBF);
+    auto run_tiles = [&](int64_t col, auto& r0, auto& r1, auto load, auto prepare, auto product) {
+        Rows w;
+        Src sa, sb;
+        auto tile = [&](int t0, const auto& cur, const auto& nxt, Src& s0, Src& s1) {
+            const bool in = t0 + n < cnt;
+            const int32_t next_a = t0 + 16 + n < cnt ? nxt.tok : -1;
+            const auto a = prepare(in, cur);
+            tile_v4f acc[NB];
+            if constexpr (!AHEAD) {
+                const int32_t tok_a = in ? cur.tok : -1;
+#pragma unroll
+                for (int c = 0; c < 8 / NB; ++c) {
+                    product(c, a, acc);
+                    if constexpr (SRC != TSRC_NONE) load_src(rows_of(tok_a), col + 64 * c, s0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) store_row(r, __shfl(tok_a, 4 * kq + r, 64), acc, col + 64 * c, s0);
+                }
+            } else if constexpr (HALVES) {
+                load_src(w, col + 64, s1);
+                product(0, a, acc);
+                store_tile(w, acc, col, s0);
+                const Rows wn = rows_of(next_a);
+                load_src(wn, col, s0);
+                product(1, a, acc);
+                store_tile(w, acc, col + 64, s1);
+                w = wn;
+            } else {
+                const Rows wn = rows_of(next_a);
+                load_src(wn, col, s1);
+                product(0, a, acc);
+                store_tile(w, acc, col, s0);
+                w = wn;
+            }
+        };
+        load(0, r0);
+        if constexpr (AHEAD) {
+            w = rows_of(n < cnt ? r0.tok : -1);
+            load_src(w, col, sa);
+        }
+        for (int t0 = 0;;) {
+            load(t0 + 16, r1);
+            tile(t0, r0, r1, sa, sb);
+            if ((t0 += 16) >= cnt) break;
+            load(t0 + 16, r0);
+            if constexpr (HALVES) tile(t0, r1, r0, sa, sb);
+            else tile(t0, r1, r0, sb, sa);
+            if ((t0 += 16) >= cnt) break;
         }
     };
 
@@ -722,9 +770,10 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
                     bj[j] = make_uint4(w4[0], w4[1], w4[2], w4[3]);
                 }
             }
-            auto tile = [&](int t0, const Raw& cur) {
-                const bool in = t0 + n < cnt;
-                const int32_t tok_a = in ? cur.tok : -1;
+            struct Parts {
+                bf16x8_t a0, a1;
+            };
+            auto prepare = [&](bool in, const Raw& cur) {
                 // this lane's parts of its eight activations
                 float av[8] = {cur.a0.x, cur.a0.y, cur.a0.z, cur.a0.w, cur.a1.x, cur.a1.y, cur.a1.z, cur.a1.w};
                 uint32_t p0[4], p1[4];
@@ -743,38 +792,25 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
                         p0[q] = part == 0 ? hi : mid;
                     }
                 }
-                const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, make_uint4(p0[0], p0[1], p0[2], p0[3]));
-                // the halves in turn (HALVES) or all eight blocks at once
+                Parts a;
+                a.a0 = __builtin_bit_cast(bf16x8_t, make_uint4(p0[0], p0[1], p0[2], p0[3]));
+                if constexpr (PARTS == 3) a.a1 = __builtin_bit_cast(bf16x8_t, make_uint4(p1[0], p1[1], p1[2], p1[3]));
+                return a;
+            };
+            auto product = [&](int c, const Parts& a, tile_v4f* acc) {
 #pragma unroll
-                for (int c = 0; c < 8 / NB; ++c) {
-                    tile_v4f acc[NB];
+                for (int j = 0; j < NB; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.a0, __builtin_bit_cast(bf16x8_t, bj[NB * c + j]),
+                                                                    tile_v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                if constexpr (PARTS == 3) {
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            a0, __builtin_bit_cast(bf16x8_t, bj[NB * c + j]), tile_v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    }
-                    if constexpr (PARTS == 3) {
-                        const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, make_uint4(p1[0], p1[1], p1[2], p1[3]));
-#pragma unroll
-                        for (int j = 0; j < NB; ++j)
-                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                a1, __builtin_bit_cast(bf16x8_t, bj[NB * c + j]), acc[j], 0, 0, 0);
-                    }
-                    store_tile(tok_a, acc, col + 64 * c);
+                    for (int j = 0; j < NB; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.a1, __builtin_bit_cast(bf16x8_t, bj[NB * c + j]),
+                                                                        acc[j], 0, 0, 0);
                 }
             };
-            // two operand sets in turn: the next tile's loads are in flight while
-            // this one runs, and no register copy makes the wait early
             Raw r0, r1;
-            load_tile(0, r0);
-            for (int t0 = 0;;) {
-                load_tile(t0 + 16, r1);
-                tile(t0, r0);
-                if ((t0 += 16) >= cnt) break;
-                load_tile(t0 + 16, r0);
-                tile(t0, r1);
-                if ((t0 += 16) >= cnt) break;
-            }
+            run_tiles(col, r0, r1, load_tile, prepare, product);
         }
     } else {
         const int steps = (D + 4 + VL) / 4;
@@ -810,38 +846,30 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
                 w[s][0] = *reinterpret_cast<const float4*>(static_cast<const float*>(w_out) + at);
                 w[s][1] = *reinterpret_cast<const float4*>(static_cast<const float*>(w_out) + at + (HALVES ? 64 : 4));
             }
-            auto tile = [&](int t0, const Raw& cur) {
-                const bool in = t0 + n < cnt;
-                const int32_t tok_a = in ? cur.tok : -1;
-                // the halves in turn (HALVES) or all eight blocks at once
+            struct Acts {
+                float a[FSTEPS];
+            };
+            auto prepare = [&](bool in, const Raw& cur) {
+                Acts a;
 #pragma unroll
-                for (int c = 0; c < 8 / NB; ++c) {
-                    tile_v4f acc[NB];
+                for (int s = 0; s < FSTEPS; ++s) a.a[s] = in ? pick(4 * s + kq, cur.a[s], cur.right, cur.a[s]) : 0.0f;
+                return a;
+            };
+            auto product = [&](int c, const Acts& a, tile_v4f* acc) {
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+                for (int j = 0; j < NB; ++j) acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int s = 0; s < FSTEPS; ++s) {
-                        if (s < steps) {
-                            const float a = in ? pick(4 * s + kq, cur.a[s], cur.right, cur.a[s]) : 0.0f;
+                for (int s = 0; s < FSTEPS; ++s) {
+                    if (s < steps) {
 #pragma unroll
-                            for (int j = 0; j < NB; ++j)
-                                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    a, fword(w[s][(NB * c + j) / 4], (NB * c + j) % 4), acc[j], 0, 0, 0);
-                        }
+                        for (int j = 0; j < NB; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.a[s], fword(w[s][(NB * c + j) / 4], (NB * c + j) % 4),
+                                                                          acc[j], 0, 0, 0);
                     }
-                    store_tile(tok_a, acc, col + 64 * c);
                 }
             };
             Raw r0, r1;
-            load_tile(0, r0);
-            for (int t0 = 0;;) {
-                load_tile(t0 + 16, r1);
-                tile(t0, r0);
-                if ((t0 += 16) >= cnt) break;
-                load_tile(t0 + 16, r0);
-                tile(t0, r1);
-                if ((t0 += 16) >= cnt) break;
-            }
+            run_tiles(col, r0, r1, load_tile, prepare, product);
         }
     }
 }
