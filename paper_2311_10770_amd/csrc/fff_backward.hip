@@ -818,19 +818,30 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_fixup_kernel(BwdParams p, int t
 // ---------------------------------------------------------------------------
 //
 // One workgroup per subtree of 2^sub leaves (the subtree's root at level
-// k = D - sub), one wave per 128-column group g.  The subtree's tokens are taken
+// k = D - sub) and matrix (dW_out from dy and a, dW_in from x and dl), one wave
+// per 128-column group g.  The subtree's tokens are taken
 // in sorted order, leaf by leaf, four per step of v_mfma_f32_16x16x4_f32: rows
 // are levels, the K dimension is the four tokens, and lane l supplies the pair
 // (a, dl) of token 4s + l/16 at level l%16 and that token's eight dy (x) values
 // at columns 128g + 8(l%16) .. +7 for the eight column blocks.  The
 // accumulators hold the sums for all D+1 nodes of the current path, lane l
-// receiving levels 4(l/16) .. +3 of its eight columns.  When a leaf is done the
+// receiving levels 4(l/16) .. +3 of its eight columns.  With several leaves a
+// leaf's sums are added to those of the leaves before it, so that a chain of
+// additions is as long as a leaf or as the subtree has leaves, never as all its
+// tokens.  What bounds it is the rows: every tree reads every token's x and dy
+// in an order of its own (fp32, hidden 768, 16384 tokens, 4 trees: 403 MB past
+// the L2s).  A wave holds one matrix's accumulators, half of them for the
+// running sums, and one step of loads ahead: with both matrices in a wave and
+// two steps ahead (156 registers) 4x9 at 16384 tokens took 497 us a training
+// step, so 465; two or three steps ahead are 2 and 3 % slower.  When a leaf is done the
 // rows of the nodes it completes (levels from the leaf up to the subtree root
 // whose last leaf it is) are stored and cleared; a node no token reached gets
 // a zero row.  The levels above the subtree root leave this subtree's sums in
 // part[] and are added in a fixed order by bwd_wsum_kernel.  Every dW element
 // has one writer and the order of every sum is fixed.
 constexpr int WT_WAVES_MAX = 8;
+constexpr int WT_FILL_WAVES = 3072;  // waves that fill the chip (256 CUs of 12)
+constexpr int WT_AHEAD = 2;        // operand sets of a wave
 constexpr int WT_TOP_LEVELS = 9;   // subtrees hang at level min(D, 9)
 constexpr int WT_MAX_SUB = 6;      // depth <= 15: at most 2^6 leaves per subtree
 constexpr int WT_LDS_TOK = 4096;   // token ids of a subtree staged in LDS when they fit
@@ -899,22 +910,125 @@ __device__ __forceinline__ void put8(float* dst, bool add, const float* v) {
     d[1] = b;
 }
 
-template <bool XBF, bool DYBF>
-__global__ __launch_bounds__(64 * WT_WAVES_MAX) void bwd_wtile_kernel(BwdParams p, int sub) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+// One wave's part of bwd_wtile_kernel: one matrix (MAT 0: dW_out from a and dy, 1: dW_in from dl and
+// x), the 128 columns of group g.
+template <int MAT, bool BF, bool MANY>
+__device__ __forceinline__ void wtile_rows(const BwdParams& p, int t, int64_t st, int sub, int64_t g, int64_t first,
+                                           const int32_t* s_cnt, const int32_t* s_tok, bool staged) {
+    const int lane = threadIdx.x & 63;
     const int n = lane & 15, q = lane >> 4;
-    const int t = blockIdx.y, T = p.n_trees, D = p.depth;
+    const int T = p.n_trees, D = p.depth;
     const int64_t L = int64_t(1) << D, H = p.hidden, N = p.n_nodes;
     const int k = D - sub;
+    const int64_t leaf0 = st << sub;
+    const int32_t* perm = p.perm + int64_t(t) * p.n_tokens;
+    const void* src = MAT == 0 ? p.dy : p.x;
+    float* dw = MAT == 0 ? p.dw_out : p.dw_in;
+    if (dw) dw += int64_t(t) * N * H;
+    const bool add = p.accumulate != 0;
+    const int lvl_a = n <= D ? n : D;  // this lane's level as A supplier (clamped; A is 0 past D)
+    const int64_t col = g * 128 + 8 * n;
+    tile_v4f acc[8];              // the current leaf's sums (MANY: all of a path's until its rows are complete)
+    tile_v4f sum[MANY ? 8 : 1];   // with several leaves: the sums over the leaves so far
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+    if constexpr (MANY)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+    auto done = [&](int j, int r) -> float {
+        if constexpr (MANY) return sum[j][r];
+        else return acc[j][r];
+    };
+    int64_t pos0 = first;  // sorted position of the current leaf's first token
+    for (int jl = 0; jl < (MANY ? 1 << sub : 1); ++jl) {
+        const int64_t leaf = leaf0 + jl;
+        const int32_t m = s_cnt[jl];
+        // operands of step s0 for this lane: (a, dl) of token s0 + q at its level, and that token's
+        // eight dy or x values as stored (token clamped into the leaf)
+        struct Ops {
+            float cf;
+            Raw8<BF> v;
+        };
+        auto load_ops = [&](int32_t s0, Ops& o) {
+            const int64_t pos = pos0 + (s0 + q < m ? s0 + q : 0);
+            const int32_t tok = staged ? s_tok[pos - first] : perm[pos];
+            o.cf = reinterpret_cast<const float*>(p.coef + (int64_t(tok) * T + t) * (D + 1) + lvl_a)[MAT];
+            o.v = raw8<BF>(src, int64_t(tok) * H + col);
+        };
+        auto step = [&](int32_t s0, const Ops& o) {
+            const float a = s0 + q < m && n <= D ? o.cf : 0.0f;
+            float v[8];
+            to8f<BF>(o.v, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, v[j], acc[j], 0, 0, 0);
+        };
+        if (m > 0) {
+            // operand sets in turn: WT_AHEAD - 1 steps are in flight while one runs; sched_barrier
+            // keeps each prefetch above the MFMAs it overlaps (the scheduler would otherwise sink
+            // the loads to their use)
+            Ops o[WT_AHEAD];
+#pragma unroll
+            for (int i = 0; i + 1 < WT_AHEAD; ++i) load_ops(4 * i, o[i]);
+            for (int32_t s0 = 0; s0 < m;) {
+#pragma unroll
+                for (int i = 0; i < WT_AHEAD; ++i) {
+                    if (s0 < m) {
+                        load_ops(s0 + 4 * (WT_AHEAD - 1), o[(i + WT_AHEAD - 1) % WT_AHEAD]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        step(s0, o[i]);
+                        s0 += 4;
+                    }
+                }
+            }
+        }
+        pos0 += m;
+        if constexpr (MANY)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                sum[j] += acc[j];
+                acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+            }
+        // rows this leaf completes: levels lv >= k whose node's last leaf this is
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int lv = 4 * q + r;
+            if (lv <= D && lv >= k && ((leaf + 1) & ((int64_t(1) << (D - lv)) - 1)) == 0) {
+                const int64_t node = ((leaf + L) >> (D - lv)) - 1;
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = done(j, r);
+                if (dw) put8(dw + node * H + col, add, v);
+                if constexpr (MANY)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) sum[j][r] = 0.0f;
+            }
+        }
+    }
+    // levels above the subtree root: this subtree's sums for the fix-up
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int lv = 4 * q + r;
+        if (lv < k) {
+            float* dst = p.part + (((int64_t(t) << k) + st) * k + lv) * 2 * H + col;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = done(j, r);
+            put8(dst + MAT * H, false, v);
+        }
+    }
+}
+
+template <bool XBF, bool DYBF, bool MANY>
+__global__ __launch_bounds__(64 * WT_WAVES_MAX) void bwd_wtile_kernel(BwdParams p, int sub) {
+    if (!(blockIdx.z == 0 ? p.dw_out : p.dw_in)) return;  // not asked for: its part[] is not used
+    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int t = blockIdx.y;
+    const int64_t L = int64_t(1) << p.depth;
     const int64_t st = blockIdx.x;
     const int64_t leaf0 = st << sub;
     const int32_t* cnt = p.counts + t * L;
     const int32_t* end = p.offs + t * L;  // after the placement: one past each leaf's last position
     const int32_t* perm = p.perm + int64_t(t) * p.n_tokens;
-    float* dwo = p.dw_out ? p.dw_out + int64_t(t) * N * H : nullptr;
-    float* dwi = p.dw_in ? p.dw_in + int64_t(t) * N * H : nullptr;
-    const bool add = p.accumulate != 0;
-    const int lvl_a = n <= D ? n : D;  // this lane's level as A supplier (clamped; A is 0 past D)
     // The subtree's tokens are one contiguous range of the sorted order: its
     // leaves' counts and, when the range fits, its token ids are staged in LDS
     // once for all waves.
@@ -928,118 +1042,10 @@ __global__ __launch_bounds__(64 * WT_WAVES_MAX) void bwd_wtile_kernel(BwdParams 
     if (staged)
         for (int64_t i = threadIdx.x; i < range; i += blockDim.x) s_tok[i] = perm[first + i];
     __syncthreads();
-    for (int64_t g = wave; g < H / 128; g += waves) {
-        const int64_t col = g * 128 + 8 * n;
-        tile_v4f ao[8], ai[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ao[j] = ai[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
-        int64_t pos0 = first;  // sorted position of the current leaf's first token
-        for (int jl = 0; jl < nleaf; ++jl) {
-            const int64_t leaf = leaf0 + jl;
-            const int32_t c = s_cnt[jl];
-            {
-                const int32_t m = c;
-                // operands of step s0 for this lane: (a, dl) of token s0 + q at its level,
-                // and that token's eight dy and x values as stored (token clamped into the leaf)
-                struct Ops {
-                    float2 cf;
-                    typename std::conditional<DYBF, uint4, float4[2]>::type dy;
-                    typename std::conditional<XBF, uint4, float4[2]>::type x;
-                };
-                auto load_ops = [&](int32_t s0, Ops& o) {
-                    const int64_t pos = pos0 + (s0 + q < m ? s0 + q : 0);
-                    const int32_t tok = staged ? s_tok[pos - first] : perm[pos];
-                    o.cf = p.coef[(int64_t(tok) * T + t) * (D + 1) + lvl_a];
-                    const int64_t at = int64_t(tok) * H + col;
-                    if constexpr (DYBF) {
-                        o.dy = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(p.dy) + at);
-                    } else {
-                        o.dy[0] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p.dy) + at);
-                        o.dy[1] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p.dy) + at + 4);
-                    }
-                    if constexpr (XBF) {
-                        o.x = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(p.x) + at);
-                    } else {
-                        o.x[0] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p.x) + at);
-                        o.x[1] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p.x) + at + 4);
-                    }
-                };
-                auto val = [](const auto& v, int j) -> float {
-                    if constexpr (std::is_same<typename std::decay<decltype(v)>::type, uint4>::value)
-                        return (j & 1) ? bf16_hi(word(v, j >> 1)) : bf16_lo(word(v, j >> 1));
-                    else
-                        return fword(v[j >> 2], j & 3);
-                };
-                auto step = [&](int32_t s0, const Ops& o) {
-                    const bool in = s0 + q < m && n <= D;
-                    const float a = in ? o.cf.x : 0.0f, dl = in ? o.cf.y : 0.0f;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        ao[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, val(o.dy, j), ao[j], 0, 0, 0);
-                        ai[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(dl, val(o.x, j), ai[j], 0, 0, 0);
-                    }
-                };
-                if (m > 0) {
-                    // three operand sets in turn: two steps are in flight while one runs;
-                    // sched_barrier keeps each prefetch above the MFMAs it overlaps (the
-                    // scheduler would otherwise sink the loads to their use)
-                    Ops o0, o1, o2;
-                    load_ops(0, o0);
-                    load_ops(4, o1);
-                    for (int32_t s0 = 0;;) {
-                        load_ops(s0 + 8, o2);
-                        __builtin_amdgcn_sched_barrier(0);
-                        step(s0, o0);
-                        if ((s0 += 4) >= m) break;
-                        load_ops(s0 + 8, o0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        step(s0, o1);
-                        if ((s0 += 4) >= m) break;
-                        load_ops(s0 + 8, o1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        step(s0, o2);
-                        if ((s0 += 4) >= m) break;
-                    }
-                }
-            }
-            pos0 += c;
-            // rows this leaf completes: levels lv >= k whose node's last leaf this is
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int lv = 4 * q + r;
-                if (lv <= D && lv >= k && ((leaf + 1) & ((int64_t(1) << (D - lv)) - 1)) == 0) {
-                    const int64_t node = ((leaf + L) >> (D - lv)) - 1;
-                    float v[8];
-                    if (dwo) {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) v[j] = ao[j][r];
-                        put8(dwo + node * H + col, add, v);
-                    }
-                    if (dwi) {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) v[j] = ai[j][r];
-                        put8(dwi + node * H + col, add, v);
-                    }
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) ao[j][r] = ai[j][r] = 0.0f;
-                }
-            }
-        }
-        // levels above the subtree root: this subtree's sums for the fix-up
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int lv = 4 * q + r;
-            if (lv < k) {
-                float* dst = p.part + (((int64_t(t) << k) + st) * k + lv) * 2 * H + col;
-                float v[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = ao[j][r];
-                put8(dst, false, v);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = ai[j][r];
-                put8(dst + H, false, v);
-            }
-        }
+    const int64_t groups = p.hidden / 128;
+    for (int64_t g = wave; g < groups; g += waves) {
+        if (blockIdx.z == 0) wtile_rows<0, DYBF, MANY>(p, t, st, sub, g, first, s_cnt, s_tok, staged);
+        else wtile_rows<1, XBF, MANY>(p, t, st, sub, g, first, s_cnt, s_tok, staged);
     }
 }
 
@@ -1911,6 +1917,18 @@ static int64_t bwd_chunks(int64_t n_tokens, int32_t depth) {
 // hidden a multiple of 128; it hangs its subtrees at level min(depth, WT_TOP_LEVELS).
 static bool wtile_shape(int32_t depth, int32_t hidden) { return depth <= 15 && hidden % 128 == 0; }
 static int wtile_k(int32_t depth) { return std::min<int32_t>(depth, WT_TOP_LEVELS); }
+// The weight kernel by itself hangs them higher where the waves of the level above (a workgroup of
+// hidden / 128, at most eight, per subtree, tree and matrix) still fill three quarters of the chip:
+// each level less halves the sums that go to the fix-up and back, and a leaf's tokens follow each
+// other (fp32, hidden 768, 4 trees of depth 9, 16384 tokens: subtrees at level 9 in 97 us and 23 in
+// the fix-up, at level 6 in 82 and 8; at hidden 256, where a workgroup has two waves, a whole
+// backward takes 145 us with level 6 and 128 with level 7).  Never below depth - WT_MAX_SUB.
+static int wtile_k(int32_t depth, int32_t n_trees, int32_t hidden) {
+    int k = wtile_k(depth);
+    const int64_t waves = 2 * int64_t(n_trees) * std::min(hidden / 128, WT_WAVES_MAX);
+    while (k > 0 && depth - (k - 1) <= WT_MAX_SUB && (waves << (k - 1)) >= WT_FILL_WAVES) --k;
+    return k;
+}
 
 size_t bwd_workspace_bytes(int64_t n_tokens, int32_t depth, int32_t n_trees, int32_t hidden) {
     const size_t recs = size_t(n_tokens) * size_t(n_trees);
@@ -2002,6 +2020,14 @@ static hipError_t launch_sort(BwdParams& p, bool count_leaves, const int64_t cap
                            stream);
 }
 
+template <bool MANY>
+static const void* wtile_kernel_for(const BwdParams& p) {
+    return p.x_bf16 ? (p.dy_bf16 ? reinterpret_cast<const void*>(&bwd_wtile_kernel<true, true, MANY>)
+                                 : reinterpret_cast<const void*>(&bwd_wtile_kernel<true, false, MANY>))
+                    : (p.dy_bf16 ? reinterpret_cast<const void*>(&bwd_wtile_kernel<false, true, MANY>)
+                                 : reinterpret_cast<const void*>(&bwd_wtile_kernel<false, false, MANY>));
+}
+
 hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, int* status) {
     *status = ST_OK_;
     const BwdVariant* v = nullptr;
@@ -2082,15 +2108,12 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
     hipError_t e = launch_sort(p, false, cap, stream);
     if (e != hipSuccess) return e;
     if (wtile_shape(p.depth, p.hidden)) {  // weight sums on MFMA, leaf by leaf
-        const int k = wtile_k(p.depth);
+        const int k = wtile_k(p.depth, p.n_trees, p.hidden);
         int sub = p.depth - k;
-        const void* kern = p.x_bf16 ? (p.dy_bf16 ? reinterpret_cast<const void*>(&bwd_wtile_kernel<true, true>)
-                                                 : reinterpret_cast<const void*>(&bwd_wtile_kernel<true, false>))
-                                    : (p.dy_bf16 ? reinterpret_cast<const void*>(&bwd_wtile_kernel<false, true>)
-                                                 : reinterpret_cast<const void*>(&bwd_wtile_kernel<false, false>));
+        const void* kern = sub > 0 ? wtile_kernel_for<true>(p) : wtile_kernel_for<false>(p);
         const int waves = std::min(p.hidden / 128, WT_WAVES_MAX);
         void* wargs[] = {&p, &sub};
-        e = hipLaunchKernel(kern, dim3(unsigned(int64_t(1) << k), p.n_trees), dim3(64 * waves), wargs, 0, stream);
+        e = hipLaunchKernel(kern, dim3(unsigned(int64_t(1) << k), p.n_trees, 2), dim3(64 * waves), wargs, 0, stream);
         if (e != hipSuccess) return e;
         return launch_wsum(p, k, stream);
     }

@@ -285,6 +285,34 @@ def test_weight_sum_pieces(fff_lib, B, D, T):
         assert np.array_equal(got[k].astype(np.float64), ref[k]), k
 
 
+@pytest.mark.parametrize("xd,wd,H,D,T", [("f32", "f32", 768, 9, 4), ("f32", "f32", 128, 6, 9), ("f32", "f32", 1152, 6, 12),
+                                         ("bf16", "f32", 256, 10, 3), ("f32", "bf16", 1024, 8, 2),
+                                         ("bf16", "bf16", 384, 7, 16), ("f32", "f32", 768, 13, 1)])
+def test_weight_sum_subtrees(fff_lib, xd, wd, H, D, T):
+    """The leaf-tiled weight sums with subtrees of one leaf and of several, hung where the trees' number
+    and the width put them, most leaves empty or of a few tokens: exact integer sums onto integers, both
+    matrices together and each by itself."""
+    B = 1500
+    L = int_layer(380 + H + D, B, H, D, T, wd)
+    L["x"] = synth.as_dtype(np.random.default_rng(7).integers(-2, 3, (B, H)).astype(np.float32), xd)
+    dy = np.random.default_rng(8).integers(-3, 4, (B, H)).astype(np.float32)
+    fwd = oracle.forward(L["x"], L["w_in"], L["w_out"], D, T, act="identity")
+    leaves, logits = fwd["nodes"][:, :, D].astype(np.int32), fwd["logits"].astype(np.float32)
+    rng = np.random.default_rng(9)
+    init = {k: rng.integers(-9, 10, s).astype(np.float32) for k, s in
+            (("dx", (B, H)), ("dw_in", L["w_in"].shape), ("dw_out", L["w_out"].shape))}
+    got = run_bwd(fff_lib, L, D, T, dy, leaves, logits, act="identity")
+    acc = run_bwd(fff_lib, L, D, T, dy, leaves, logits, act="identity", accumulate=True, init=init)
+    ref = oracle.backward(L["x"], L["w_in"], L["w_out"], D, T, dy, fwd["nodes"], act="identity")
+    for k in ("dx", "dw_in", "dw_out"):
+        assert np.array_equal(got[k].astype(np.float64), ref[k]), k
+        assert np.array_equal(acc[k].astype(np.float64), ref[k] + init[k]), k
+    for k in ("dw_in", "dw_out"):
+        one = fff_lib.backward(dev(fff_lib, L["x"]), dev(fff_lib, L["w_in"]), dev(fff_lib, L["w_out"]), D, T,
+                               dev(fff_lib, dy), dev(fff_lib, leaves), dev(fff_lib, logits), act="identity", want=(k,))
+        assert np.array_equal(fff_lib.to_numpy(one[("dx", "dw_in", "dw_out").index(k)]), got[k]), k
+
+
 @pytest.mark.parametrize("H", [128, 256, 640, 768, 896])
 @pytest.mark.parametrize("B,D", [(1, 6), (33, 0), (700, 3), (2500, 5), (600, 12), (300, 15)])
 def test_fused_bf16_widths(fff_lib, H, B, D):
