@@ -8,8 +8,8 @@
 // LDS with global_load_lds_dwordx4 (no registers in between, one step in
 // flight while the previous one is multiplied), in an XOR-swizzled layout that
 // keeps the fragment reads free of bank conflicts (fff_gemm.hpp); a workgroup of
-// four waves computes a 256 x 256 (128 x 128 per wave), 256 x 192 or 128 x 128
-// tile, and consecutive tiles of one row block of A run on one XCD.  A partial
+// eight waves computes a 256 x 256 (128 x 64 per wave) or 256 x 192 tile, or one of
+// four (or eight) a 128 x 128 tile, and consecutive tiles of one row block of A run on one XCD.  A partial
 // last step of K is loaded through registers with zeros past K.  Every 16x16
 // MFMA returns D[4(l/16)+r][l%16] to lane l, register r; its bf16 operands are
 // A[l%16][8(l/16) .. +7] and
@@ -152,12 +152,18 @@ void launch_dma(const void* A, const void* B, void* C, const void* src, int64_t 
                        A, B, C, src, M, N, K, lda, ldb, ldc, splits > 1 ? kchunk : K, act);
 }
 
-// Tile choice, from the shapes and the CU count only: 256 x 256 tiles (128 x 128 per wave, bf16)
-// or 256 x 192 (128 x 96 per wave), one workgroup per CU, whichever leaves fewer tile-rounds of
-// idle CUs (the narrower tile reads ~7% more LDS per MFMA; its fp32 form is the only wide one
-// that needs no spills), or 128 x 128 tiles with two workgroups per CU for small products and
-// for the activation forms, whose epilogue evaluates the activation of every value it stores:
-// at one workgroup per CU that chain of dependent instructions has nothing to hide under.  A
+// Tile choice, from the shapes and the CU count only: 256 x 256 tiles (128 x 64 per wave, bf16)
+// or 256 x 192 (64 x 96 per wave), one workgroup of eight waves per CU, whichever leaves fewer
+// tile-rounds of idle CUs (the narrower tile reads more LDS per MFMA; it is the only wide fp32
+// form), or 128 x 128 tiles with two workgroups per CU for small products and for the activation
+// forms, whose epilogue evaluates the activation of every value it stores: at one workgroup per CU
+// that chain of dependent instructions has nothing to hide under.  Two waves per SIMD: one's barrier,
+// LDS reads and stores run under the other's MFMAs, which is worth more than the LDS reads that
+// four waves of twice the tile would save (256 trees of depth 3, bf16, hidden 768, 16384 tokens:
+// first product 163 us with four waves, 135 with eight; second 244 and 214; fp32 1 to 5 % of a
+// forward).  The bf16 activation form takes eight waves of 64 x 32 for the same reason (768 trees of
+// depth 0, 65536 tokens: 373 and 334 us a forward; other products of 128 x 128 tiles and fp32 gain
+// nothing or lose up to 4 %).  A
 // small product with too few tiles for the CUs and a long K is split along K into chunks of
 // whole steps (at least four each), up to two workgroups per CU and the partial sums' buffer,
 // and reduced in split order: the split depends on the shapes, the CU count and split_bytes only.
@@ -185,17 +191,20 @@ hipError_t launch_gemm(const void* A, const void* B, void* C, const void* src, i
                                static_cast<const float*>(split_ws), int(splits), C, src, M, N, ldc, act);
             return hipGetLastError();
         }
-        launch_dma<BF, 4, 4, 2, 2, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
+        if constexpr (BF && OUT >= GOUT_ACT_F32)
+            launch_dma<BF, 4, 2, 2, 4, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
+        else
+            launch_dma<BF, 4, 4, 2, 2, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
         return hipGetLastError();
     }
     if constexpr (OUT < GOUT_ACT_F32) {
         if constexpr (BF) {
             if (double(cdiv(t88, slots)) * 256 * 256 <= double(cdiv(t86, slots)) * 256 * 192 * 1.07) {
-                launch_dma<BF, 8, 8, 2, 2, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
+                launch_dma<BF, 8, 4, 2, 4, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
                 return hipGetLastError();
             }
         }
-        launch_dma<BF, 8, 6, 2, 2, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
+        launch_dma<BF, 4, 6, 4, 2, 2, OUT, DBF>(A, B, C, src, M, N, K, lda, ldb, ldc, act, stream);
     }
     return hipGetLastError();
 }

@@ -630,6 +630,15 @@ def test_masked_f32_shapes(fff_lib, k, d, B):
     check_layer(fff_lib, f"masked f32 {k}x{d} B={B}", L, d, k, "f32", mode="masked")
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("k,d,B,H", [(340, 1, 4099, 72), (70, 1, 3399, 1032), (86, 1, 5000, 520), (200, 0, 385, 264)])
+def test_masked_wide_tiles(fff_lib, dt, k, d, B, H):
+    """Products on the eight-wave tiles (256 x 256 and 256 x 192, and 128 x 128 with the activation in
+    the store) with remainders in every extent and a partial last step of K."""
+    L = layer(480 + H, B, H, d, k, dt, dt)
+    check_layer(fff_lib, f"masked wide {dt} {k}x{d} B={B} H={H}", L, d, k, dt, mode="masked")
+
+
 @pytest.mark.parametrize("dt,H", [("bf16", 200), ("bf16", 8), ("f32", 104), ("f32", 8)])
 def test_masked_ragged_hidden(fff_lib, dt, H):
     """A hidden size that is not a whole number of the products' K steps (64 bf16 or 32 fp32
