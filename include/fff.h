@@ -75,8 +75,12 @@ typedef enum { FFF_ACT_GELU_ERF = 0, FFF_ACT_GELU_TANH = 1, FFF_ACT_IDENTITY = 2
  * handled by the workgroups of one XCD so that its rows stay in that XCD's L2.
  * With 2, 4 or 8 trees (GROUPED and TILED) each walk workgroup walks the tree
  * of its XCD, with that tree's top levels in LDS.
- * GENERIC: any hidden size, one wave per token.
- * TILED: 1..16 trees, depth 5..15, hidden a multiple of 128: the walk drops
+ * GENERIC: any hidden size; rows of whole 16-byte vectors as a fused descent
+ * with the row length as a run-time value, other rows a wave per token.
+ * TILED (large batches of bf16 x, W and y through one tree of depth at most 11,
+ * hidden a multiple of 128 up to 1024, take the tree's subtrees as dense
+ * products on MFMA instead of what follows):
+ * 1..16 trees, depth 5..15, hidden a multiple of 128: the walk drops
  * each token into a bucket of its leaf in every tree, and the output rows of up
  * to 16 tokens that share a leaf (hence all D+1 nodes) are accumulated as one
  * dense product on MFMA, one launch per tree in tree order, each adding its
