@@ -641,9 +641,12 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
     // AHEAD: the source rows of the next half (or tile) are loaded before this one's stores: memory
     // operations retire in order, and a load behind the stores would be waited for with them (the later
     // trees of a 4x9 layer, fp32, 16384 tokens: 27.2 -> 23.0 us a tree; residual of fp32 x with bf16
-    // weights, depth 11, 65536 tokens: 181 -> 159 us).  Not for leaf pairs with a bf16 destination,
-    // mostly one tile each: the registers cost a wave per SIMD (depth 13, 8192 tokens 52 -> 58 us).
-    constexpr bool AHEAD = SRC != TSRC_NONE && !(PAIR && DBF);
+    // weights, depth 11, 65536 tokens: 181 -> 159 us).  Not where the registers cost more waves than that
+    // gains: leaf pairs with a bf16 destination, mostly one tile each (depth 13, 8192 tokens 52 -> 58
+    // us), and the last tree of several with one (two trees of depth 11, bf16, 32768 tokens: a forward
+    // 115.3 without, 119.6 with).  At hidden 1024 two or four fp32 trees gain 2 % at 32 tokens per leaf and
+    // lose as much at 64; one tree's residual, the same kernel, gains 2 to 4 %.
+    constexpr bool AHEAD = SRC != TSRC_NONE && !(DBF && (PAIR || SRC == TSRC_F32));
     auto run_tiles = [&](int64_t col, auto& r0, auto& r1, auto load, auto prepare, auto product) {
         Rows w;
         Src sa, sb;
@@ -846,30 +849,73 @@ __global__ __launch_bounds__(64 * tile_waves(16 * CB)) void tile_kernel(Params p
                 w[s][0] = *reinterpret_cast<const float4*>(static_cast<const float*>(w_out) + at);
                 w[s][1] = *reinterpret_cast<const float4*>(static_cast<const float*>(w_out) + at + (HALVES ? 64 : 4));
             }
-            struct Acts {
-                float a[FSTEPS];
-            };
-            auto prepare = [&](bool in, const Raw& cur) {
-                Acts a;
-#pragma unroll
-                for (int s = 0; s < FSTEPS; ++s) a.a[s] = in ? pick(4 * s + kq, cur.a[s], cur.right, cur.a[s]) : 0.0f;
-                return a;
-            };
-            auto product = [&](int c, const Acts& a, tile_v4f* acc) {
-#pragma unroll
-                for (int j = 0; j < NB; ++j) acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < FSTEPS; ++s) {
-                    if (s < steps) {
-#pragma unroll
-                        for (int j = 0; j < NB; ++j)
-                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.a[s], fword(w[s][(NB * c + j) / 4], (NB * c + j) % 4),
-                                                                          acc[j], 0, 0, 0);
-                    }
-                }
-            };
             Raw r0, r1;
-            run_tiles(col, r0, r1, load_tile, prepare, product);
+            if constexpr (SRC == TSRC_NONE) {
+                // no source rows: each step's operand formed where the step runs, a row's offset whatever its
+                // token (through run_tiles 20.2 us in place of 19.5 at depth 11, 16384 tokens)
+                auto tile = [&](int t0, const Raw& cur) {
+                    const bool in = t0 + n < cnt;
+                    const int32_t tok_a = in ? cur.tok : -1;
+#pragma unroll
+                    for (int c = 0; c < 8 / NB; ++c) {
+                        tile_v4f acc[NB];
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int s = 0; s < FSTEPS; ++s) {
+                            if (s < steps) {
+                                const float a = in ? pick(4 * s + kq, cur.a[s], cur.right, cur.a[s]) : 0.0f;
+#pragma unroll
+                                for (int j = 0; j < NB; ++j)
+                                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                        a, fword(w[s][(NB * c + j) / 4], (NB * c + j) % 4), acc[j], 0, 0, 0);
+                            }
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int32_t tok = __shfl(tok_a, 4 * kq + r, 64);
+                            const uint32_t at = uint32_t((int64_t(tok) * H + col + 64 * c) * DSZ);
+                            float v[NB];
+#pragma unroll
+                            for (int j = 0; j < NB; ++j) v[j] = acc[j][r];
+                            tile_store_buf<SRC, DBF, NB>(TileSrc<SRC, NB>{}, rdst, tok >= 0 ? at : TILE_NO_ROW, v);
+                        }
+                    }
+                };
+                load_tile(0, r0);
+                for (int t0 = 0;;) {
+                    load_tile(t0 + 16, r1);
+                    tile(t0, r0);
+                    if ((t0 += 16) >= cnt) break;
+                    load_tile(t0 + 16, r0);
+                    tile(t0, r1);
+                    if ((t0 += 16) >= cnt) break;
+                }
+            } else {
+                struct Acts {
+                    float a[FSTEPS];
+                };
+                auto prepare = [&](bool in, const Raw& cur) {
+                    Acts a;
+#pragma unroll
+                    for (int s = 0; s < FSTEPS; ++s) a.a[s] = in ? pick(4 * s + kq, cur.a[s], cur.right, cur.a[s]) : 0.0f;
+                    return a;
+                };
+                auto product = [&](int c, const Acts& a, tile_v4f* acc) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) acc[j] = tile_v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int s = 0; s < FSTEPS; ++s) {
+                        if (s < steps) {
+#pragma unroll
+                            for (int j = 0; j < NB; ++j)
+                                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.a[s], fword(w[s][(NB * c + j) / 4], (NB * c + j) % 4),
+                                                                              acc[j], 0, 0, 0);
+                        }
+                    }
+                };
+                run_tiles(col, r0, r1, load_tile, prepare, product);
+            }
         }
     }
 }
