@@ -324,7 +324,7 @@ int fff_forward_stack(const fff_args* a, const fff_layer* layers, int32_t n_laye
  * are the same bits on every run.
  */
 typedef struct {
-    const void* x;          /* [n_tokens, hidden] the layer's FFF input (x_dtype) */
+    const void* x;          /* [n_tokens, hidden] the layer's FFF input (x_dtype); may be NULL when dW_in is */
     const void* W_in;       /* [n_trees, N, hidden] (w_dtype) */
     const void* W_out;
     const void* dy;         /* [n_tokens, hidden] upstream gradient (dy_dtype) */

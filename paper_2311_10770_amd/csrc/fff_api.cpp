@@ -401,7 +401,9 @@ int validate_backward(const fff_backward_args* a, fff::BwdParams* p) {
                 if (overlap(a->workspace, int64_t(need), q.ptr, q.bytes)) return FFF_ERR_INVALID_ARG;
         }
     }
-    p->x = a->x;
+    // x enters dW_in alone and may be absent without it; some kernels form both matrices' sums whichever
+    // is wanted, so dy, of the same shape, stands for an absent x (those sums are never stored in dW_in)
+    p->x = a->x ? a->x : a->dy;
     p->w_in = a->W_in;
     p->w_out = a->W_out;
     p->dy = a->dy;
@@ -416,7 +418,7 @@ int validate_backward(const fff_backward_args* a, fff::BwdParams* p) {
     p->hidden = a->hidden;
     p->depth = a->depth;
     p->n_trees = a->n_trees;
-    p->x_bf16 = a->x_dtype == FFF_BF16;
+    p->x_bf16 = (a->x ? a->x_dtype : a->dy_dtype) == FFF_BF16;
     p->w_bf16 = a->w_dtype == FFF_BF16;
     p->dy_bf16 = a->dy_dtype == FFF_BF16;
     p->dx_bf16 = a->dx_dtype == FFF_BF16;

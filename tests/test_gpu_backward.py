@@ -339,6 +339,28 @@ def test_fused_bf16_widths(fff_lib, H, B, D):
         assert np.array_equal(acc[k].astype(np.float64), ref[k] + init[k]), k
 
 
+@pytest.mark.parametrize("H,D,T,wd,yd", [
+    (768, 5, 1, "bf16", "bf16"), (128, 5, 1, "bf16", "bf16"), (1024, 11, 1, "bf16", "bf16"),  # fused, both kernels
+    (768, 6, 1, "bf16", "f32"),   # fused, fp32 dy
+    (768, 4, 3, "f32", "f32"),    # leaf-tiled weight sums
+    (300, 4, 2, "f32", "f32"), (264, 4, 2, "bf16", "bf16"), (20, 3, 1, "bf16", "f32")])  # pieces
+def test_no_x_without_dw_in(fff_lib, H, D, T, wd, yd):
+    """x may be absent when dW_in is not wanted: the outputs are those of the same call with x."""
+    B = 333
+    L = synth.make_layer(390 + H + D, B, H, D, T, yd, wd)
+    fwd = oracle.forward(L["x"], L["w_in"], L["w_out"], D, T)
+    args = [dev(fff_lib, a) for a in (L["w_in"], L["w_out"])] + [D, T] + [
+        dev(fff_lib, a) for a in (synth.make_x(391, B, H, yd), fwd["nodes"][:, :, D].astype(np.int32),
+                                  fwd["logits"].astype(np.float32))]
+    for want in (("dx", "dw_out"), ("dw_out",), ("dx",)):
+        flush_print(f"[gpu] bwd without x H={H} D={D} T={T} {wd}/{yd} {want}")
+        given = fff_lib.backward(dev(fff_lib, L["x"]), *args, want=want)
+        got = fff_lib.backward(None, *args, want=want)
+        torch.cuda.synchronize()
+        for a, b in zip(given, got):
+            assert (a is None and b is None) or torch.equal(a, b), want
+
+
 def test_fused_bf16_nan_stays_with_its_token(fff_lib):
     """A nan in one token's x (dy) reaches that token's dx and its own path's dW rows only."""
     B, H, D = 900, 768, 5
