@@ -1515,7 +1515,7 @@ int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_
         plan->split_level = std::min<int>(p.depth - 2, 5);  // subtrees of at least four leaves
         plan->name = v->name;
         plan->tile_pair = tile_pairs(p) ? 1 : 0;
-        plan->dense = dense_plan(p);
+        plan->dense = lds_levels_req == 0 && dense_plan(p);  // a request for LDS levels is the walk's to grant or refuse
         plan->cu_count = dev.cu_count;
         if (plan->dense) return ST_OK;
         const int64_t leaves = int64_t(1) << p.depth;

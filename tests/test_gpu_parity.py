@@ -1018,6 +1018,19 @@ def test_tiled_dense_plan(fff_lib):
     assert dense_of(fff_lib, x, w12, w12, 12) == 0
 
 
+def test_tiled_dense_lds_levels(fff_lib):
+    """A request for levels in LDS is the walk's: refused past the tree or the LDS, obeyed otherwise."""
+    w = torch.zeros(1, 4095, 768, dtype=torch.bfloat16, device=DEV)
+    x = torch.zeros(65536, 768, dtype=torch.bfloat16, device=DEV)
+    assert dense_of(fff_lib, x, w, w, 11) == 1
+    for levels in (13, 12, 25):  # past the tree; 6 MB of rows
+        with pytest.raises(fff_lib.FffError):
+            fff_lib.describe(x, w, w, 11, 1, mode="tiled", lds_levels=levels)
+    for levels, want in ((-1, 0), (2, 2)):
+        plan = fff_lib.describe(x, w, w, 11, 1, mode="tiled", lds_levels=levels)
+        assert "dense=0" in plan and f" lds_levels={want} " in plan, plan
+
+
 @pytest.mark.parametrize("D,B", [(5, 4100), (11, 49200)])
 @pytest.mark.parametrize("out", ["residual", "accumulate", "in place"])
 def test_tiled_dense_output_modes(fff_lib, D, B, out):
