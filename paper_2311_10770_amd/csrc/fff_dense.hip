@@ -52,8 +52,10 @@ constexpr int DN_MAX_LEVELS = 6;             // levels of a subtree: at most 64 
 constexpr int DN_REC = 8;                    // floats per token of the top pass's activations
 constexpr int DN_MAX_HIDDEN = 1024;          // W_out of a subtree fits LDS
 constexpr int DN_SC = 65;                    // floats per token of the logits in LDS (odd: lanes read one column)
-constexpr int64_t DN_CHUNK = 98304;          // most tokens per pair of passes (768 top workgroups)
-constexpr int64_t DN_CHUNK_MEAN = 65536;     // larger batches: pairs of passes of about this many
+// Most tokens per pair of passes: however they fall into 64 groups, workgroups of DS_TOK tokens are no more
+// than a round of 256 CUs (below).  Larger batches: as many equal chunks as it takes.
+constexpr int64_t DN_CHUNK = 69632;
+static_assert(DN_CHUNK / DS_TOK + (1 << DN_MAX_LEVELS) <= 256, "one round of subtree workgroups");
 
 // What the two passes hand over, carved from the workspace.
 struct DenseArgs {
@@ -64,7 +66,8 @@ struct DenseArgs {
     int32_t top_wgs;
     int32_t s;         // levels of the top pass (0: none)
     int32_t levels;    // levels of the subtree pass
-    int32_t item;      // most tokens of a subtree workgroup
+    int32_t item;      // most tokens of a subtree workgroup (s == 0), or the fewest such bound
+    int32_t round;     // subtree workgroups that run at once
     float* act;        // [B, DN_REC] activations of levels s .. D and, last, the subtree column of the leaf
 };
 
@@ -364,7 +367,7 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_sub_kernel(Params p, Dens
         int32_t* s_tot = s_pre + 4 * DS_THREADS;
         uint4* s_hist = reinterpret_cast<uint4*>(s_tot + 8);  // [2^s][hist_ld / 16]
         {
-            constexpr int UN = DN_CHUNK / DT_TOK / 16 / 8;  // 16-byte vectors per thread
+            constexpr int UN = (DN_CHUNK / DT_TOK / 16 + 7) / 8;  // 16-byte vectors per thread
             const int gg = tid >> 3, hv = a.hist_ld / 16;
             const bool live = gg < (1 << s);
             const uint4* h = reinterpret_cast<const uint4*>(a.hist + int64_t(live ? gg : 0) * a.hist_ld);
@@ -386,9 +389,19 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_sub_kernel(Params p, Dens
             if ((tid & 7) == 0) s_cnt[gg] = int32_t(sum);
         }
         __syncthreads();
-        // items: ceil(count / a.item) per group, groups in order; XCD x (blockIdx % 8) takes a
-        // contiguous eighth of them, so that a group's rows are read through one L2
-        const int cnt = s_cnt[lane], items = (cnt + a.item - 1) / a.item;
+        // items: ceil(count / most) per group, groups in order, with the smallest bound (a multiple of 16)
+        // whose items all run at once: the groups' sizes are the routing's, and one item more than the
+        // CUs take would cost a second round (bounds from the mean size, an eighth to spare: depth 11,
+        // hidden 768, 57344 / 61440 / 65536 tokens 102 / 107 / 80 us a forward; so 75 / 78 / 82).  XCD x
+        // (blockIdx % 8) takes a contiguous eighth of them, so that a group's rows are read through one L2
+        const int cnt = s_cnt[lane];
+        int lo16 = a.item / 16, hi16 = int(p.n_tokens) / a.item + (1 << s) <= a.round ? lo16 : TOK / 16;
+        while (lo16 < hi16) {
+            const int most = (lo16 + hi16) / 2 * 16;
+            if (__builtin_amdgcn_readlane(wave_scan((cnt + most - 1) / most, lane), 63) <= a.round) hi16 = most / 16;
+            else lo16 = most / 16 + 1;
+        }
+        const int items = (cnt + 16 * lo16 - 1) / (16 * lo16);
         const int incl = wave_scan(items, lane);
         const int total = __builtin_amdgcn_readlane(incl, 63);
         const int x = int(blockIdx.x % XCDS), i = int(blockIdx.x / XCDS);
@@ -700,16 +713,14 @@ size_t dense_workspace_bytes(int64_t n_tokens) {
     return 2 * align256(n * DN_REC * sizeof(float)) + align256(wgs * DT_TOK) + align256(ld << DN_MAX_LEVELS);
 }
 
-// Most tokens of a subtree workgroup (a multiple of 16): the mean group over a number of workgroups
-// that fills the CUs, with an eighth to spare so that the usual spread of the groups' sizes does not
-// add workgroups to a full round.
-static int dense_item(int64_t n_tokens, int s, int cu_count) {
-    const double mean = double(n_tokens) / double(int64_t(1) << s);
-    const int64_t per = std::max<int64_t>(1, cu_count >> s);  // workgroups per group and round
+constexpr int DN_ITEM_MIN = 16 * DS_WAVES;  // a tile per wave
+
+// Tokens of a workgroup without a top pass (a multiple of 16): the batch over a number of workgroups that
+// fills the CUs.
+static int dense_item(int64_t n_tokens, int cu_count) {
     int64_t item = DS_TOK + 1;
-    for (int64_t k = per; item > DS_TOK; k += per)
-        item = int64_t(mean * (s ? 1.125 : 1.0) / double(k) / 16.0 + 1.0) * 16;
-    return int(std::max<int64_t>(item, 128));
+    for (int64_t k = cu_count; item > DS_TOK; k += cu_count) item = (n_tokens / k / 16 + 1) * 16;
+    return int(std::max<int64_t>(item, DN_ITEM_MIN));
 }
 
 hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t stream) {
@@ -724,9 +735,10 @@ hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t
                                             : reinterpret_cast<const void*>(&dense_sub_kernel<2, false>));
     const size_t sub_lds = sub > 5 ? DSub<4>::lds(p.hidden) : DSub<2>::lds(p.hidden);
     const int64_t H = p.hidden;
+    const int cus = cu_count > 0 ? cu_count : 256;
     // pairs of passes over equal chunks
-    const int64_t chunks = std::max<int64_t>(1, (p.n_tokens + DN_CHUNK_MEAN / 2) / DN_CHUNK_MEAN);
-    const int64_t chunk = (p.n_tokens + chunks - 1) / chunks;  // below 1.5 DN_CHUNK_MEAN = DN_CHUNK
+    const int64_t chunks = (p.n_tokens + DN_CHUNK - 1) / DN_CHUNK;
+    const int64_t chunk = (p.n_tokens + chunks - 1) / chunks;
     for (int64_t c0 = 0; c0 < p.n_tokens; c0 += chunk) {
         Params c = p;
         c.n_tokens = std::min(chunk, p.n_tokens - c0);
@@ -749,14 +761,17 @@ hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t
         a.hist_ld = int32_t((wgs + 15) / 16 * 16);
         a.s = s;
         a.levels = sub;
-        a.item = dense_item(c.n_tokens, s, cu_count > 0 ? cu_count : 256);
+        a.item = s ? DN_ITEM_MIN : dense_item(c.n_tokens, cus);
+        a.round = cus;
         void* args[] = {&c, &a};
         if (s) {
             const hipError_t e = hipLaunchKernel(top, dim3(unsigned(wgs)), dim3(64 * DT_WAVES), args, top_lds, stream);
             if (e != hipSuccess) return e;
         }
-        // at most one item per whole a.item tokens and one partly filled per group
-        const int64_t items = c.n_tokens / a.item + (int64_t(1) << s);
+        // at most one item per whole `most` tokens and one partly filled per group: a.round of them, or
+        // with the bound at its least or its most
+        const int64_t groups = int64_t(1) << s;
+        const int64_t items = std::min(c.n_tokens / a.item + groups, std::max<int64_t>(a.round, c.n_tokens / DS_TOK + groups));
         const int64_t grid = s ? (items + XCDS - 1) / XCDS * XCDS : (c.n_tokens + a.item - 1) / a.item;
         const hipError_t e = hipLaunchKernel(subk, dim3(unsigned(grid)), dim3(DS_THREADS), args, sub_lds, stream);
         if (e != hipSuccess) return e;

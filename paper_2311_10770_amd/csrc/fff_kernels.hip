@@ -1356,22 +1356,31 @@ static bool tile_pairs(const Params& p) {
     return p.depth >= 5 && p.depth + 2 <= 4 * TILE_MAX_STEPS && p.n_tokens < (int64_t(16) << p.depth);
 }
 
-// Subtrees as dense products (fff_dense.hip): its two passes cost about 30 us whatever the batch, so
-// it takes large ones: at depth 10 and 11 from 49152 tokens, shallower from 64 per leaf (where the tile
-// launch has few workgroups) and 4096.  Measured against the walk and the leaf tiles (bf16, buffers
-// rotating, us; hidden 768): depth 11, 40000 / 49152 / 65536 / 131072 tokens 64 / 66 / 82 / 162 against
-// 63 / 77 / 95 / 174 (hidden 1024, 65536: 101 against 124); depth 10, 49152 / 65536 / 262144: 67 / 78 /
-// 311 against 70 / 87 / 305; depth 9, 16384 / 32768 / 65536: 35 / 46 / 73 against 33 / 54 / 91; depth
-// 7, 4096 / 8192: 31 / 32 against 23 / 36; depth 5, 2048 / 4096: 24 / 24 against 22 / 31.  Not between
-// 81920 tokens (one more would start a second round of subtree workgroups) and 98304 (two pairs of
-// passes): depth 11, 90000 tokens 126 against 122.
-constexpr int64_t DENSE_TOKENS = 49152, DENSE_ROUND = 81920, DENSE_TWO = 98304;
-constexpr int64_t DENSE_MIN_TOKENS = 4096, DENSE_PER_LEAF = 64;
+// Subtrees as dense products (fff_dense.hip), where that beats the walk and the leaf tiles: at depths 10
+// and 11 from 49152 tokens, shallower from 64 per leaf (96 at hidden 1024) and enough for the CUs.  Up to
+// 69632 the subtree workgroups are one round whatever the routing; past that two rounds, at depth 11 of at
+// least 57344 each.  bf16, buffers rotating, times over those of the walk and the leaf tiles, the range
+// over four sets of weights:
+//   depth 11, hidden 768, 49152 / 57344 / 65536 / 69632 / 73728 tokens: stored 0.93 / 0.92-0.94 /
+//     0.93-0.95 / 0.97-0.98 / 1.00-1.01, residual with records 0.99-1.00 / 0.93-0.95 / 0.92-0.93 /
+//     0.93-0.95 / 0.95; hidden 1024, 0.81-0.95 and 0.88-0.95; accumulating 0.85-0.92
+//   two rounds, 98304 / 114688 / 131072: 0.98-1.00 / 0.94-0.95 / 0.93-0.94 stored, 1.00-1.02 / 0.94-0.96 /
+//     0.93-0.94 residual, 1.05 / - / 1.00 accumulating with records; three 0.97-1.07 (163840 to 229376)
+//   depth 10, hidden 768, 49152 / 65536 / 69632 / 73728: 0.93-0.95 / 0.94-0.95 / 0.99-1.00 / 1.04-1.05
+//     stored, 1.00-1.01 / 0.95 / 0.97-0.98 / 0.99-1.00 residual with records
+//   depths 6 to 9 at 64 per leaf: hidden 768 1.09-1.13 (4096 tokens; 5120 0.95-0.97) / 0.97-1.00 /
+//     0.88-0.89 / 0.86-0.91, hidden 1024 1.31-1.34 / 1.16-1.19 / 1.05-1.21 / 0.97-1.07; at 96 per leaf
+//     hidden 1024 0.99-1.03 (6144 tokens) / 0.88-0.90 / 0.83-0.87 / 0.91-1.00
+//   depth 5, 4096 tokens: 0.69-0.79, hidden 1024 0.86-0.97.
+constexpr int64_t DENSE_TOKENS = 49152, DENSE_ROUND = 69632, DENSE_TWO = 98304, DENSE_TWO_DEEP = 114688;
+constexpr int64_t DENSE_MIN_TOKENS = 4096, DENSE_MIN_BY_HIDDEN = 8, DENSE_PER_LEAF = 64, DENSE_PER_LEAF_WIDE = 96;
 static bool dense_plan(const Params& p) {
     const int64_t n = p.n_tokens;
-    const bool one = n <= DENSE_ROUND, two = n >= DENSE_TWO;
-    const bool big = n >= DENSE_TOKENS && (one || (two && p.depth >= 11));
-    const bool full = n >= DENSE_MIN_TOKENS && n >= (DENSE_PER_LEAF << p.depth) && (one || (two && p.depth <= 8));
+    const bool one = n <= DENSE_ROUND;
+    const bool big = n >= DENSE_TOKENS && (one || (p.depth >= 11 && n >= DENSE_TWO_DEEP && n <= 2 * DENSE_ROUND));
+    const int64_t least = p.depth > 5 ? DENSE_MIN_BY_HIDDEN * p.hidden : DENSE_MIN_TOKENS;
+    const int64_t per_leaf = p.hidden > 768 ? DENSE_PER_LEAF_WIDE : DENSE_PER_LEAF;
+    const bool full = n >= least && n >= (per_leaf << p.depth) && (one || (n >= DENSE_TWO && p.depth <= 8));
     return dense_shape(p) && (big || full) &&
            dense_workspace_bytes(n) <= tiled_workspace_bytes(n, p.depth, p.n_trees, p.hidden);
 }

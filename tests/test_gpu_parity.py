@@ -980,38 +980,47 @@ def dense_of(fff, x, wi, wo, D, **kw):
 
 @pytest.mark.parametrize("H,D,B", [
     (768, 5, 4096), (768, 5, 5003),       # one pass: the whole tree is the subtree
-    (768, 6, 4099), (768, 7, 8207),       # few and unevenly filled groups
-    (128, 8, 16385), (896, 9, 32769),     # one column block; an odd number of them
+    (768, 6, 6149), (768, 7, 8207),       # few and unevenly filled groups
+    (768, 8, 16385), (1024, 9, 49153),    # four and five levels below four and five
     (1024, 10, 49153), (768, 11, 50021),  # five and six levels below six
     (1024, 11, 49152)])
 def test_tiled_dense(fff_lib, H, D, B):
     """The dense form against the oracle: ragged last tiles and workgroups, every split of the levels."""
-    if H in (128, 896):  # no tiled plan at these widths: refused, whatever the batch
-        with pytest.raises(fff_lib.FffError):
-            run_fff(fff_lib, layer(300, 64, H, D, 1, "bf16", "bf16"), D, 1, "bf16", mode="tiled")
-        H = 1024 if H == 896 else 768
     L = layer(300 + D, B, H, D, 1, "bf16", "bf16")
     x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
     assert dense_of(fff_lib, x, wi, wo, D) == 1
     check_layer(fff_lib, f"tiled dense H={H} B={B} D={D}", L, D, 1, "bf16", mode="tiled")
 
 
+@pytest.mark.parametrize("H,D", [(128, 8), (896, 9)])
+def test_tiled_refused_without_a_plan_for_the_width(fff_lib, H, D):
+    with pytest.raises(fff_lib.FffError):
+        run_fff(fff_lib, layer(300, 64, H, D, 1, "bf16", "bf16"), D, 1, "bf16", mode="tiled")
+
+
 def test_tiled_dense_plan(fff_lib):
-    """From 49152 tokens, or 64 per leaf and 4096, with a gap where a second round would start; bf16 x, W
-    and y only."""
+    """From 49152 tokens, or 64 per leaf (96 at hidden 1024) and 8 x hidden (4096 at depth 5), up to one round
+    of subtree workgroups, or two; bf16 x, W and y only."""
     w = torch.zeros(1, 4095, 768, dtype=torch.bfloat16, device=DEV)
     x = torch.zeros(49152, 768, dtype=torch.bfloat16, device=DEV)
     assert dense_of(fff_lib, x, w, w, 11) == 1 and dense_of(fff_lib, x[:49151], w, w, 11) == 0
     w7 = w[:, :255].contiguous()
     assert dense_of(fff_lib, x[:8192], w7, w7, 7) == 1 and dense_of(fff_lib, x[:8191], w7, w7, 7) == 0
+    w6 = w[:, :127].contiguous()
+    assert dense_of(fff_lib, x[:6144], w6, w6, 6) == 1 and dense_of(fff_lib, x[:6143], w6, w6, 6) == 0
     w5 = w[:, :63].contiguous()
     assert dense_of(fff_lib, x[:4096], w5, w5, 5) == 1 and dense_of(fff_lib, x[:4095], w5, w5, 5) == 0
     assert dense_of(fff_lib, x, w, w, 11, y_dtype=torch.float32) == 0
     assert dense_of(fff_lib, x.float(), w, w, 11, y_dtype=torch.bfloat16) == 0
     assert dense_of(fff_lib, x, w, w, 11, norm="layernorm") == 0
-    big = torch.zeros(131072, 768, dtype=torch.bfloat16, device=DEV)
+    xw = torch.zeros(24576, 1024, dtype=torch.bfloat16, device=DEV)
+    for d, n in ((6, 8192), (7, 12288), (8, 24576)):
+        ww = torch.zeros(1, (2 << d) - 1, 1024, dtype=torch.bfloat16, device=DEV)
+        assert dense_of(fff_lib, xw[:n], ww, ww, d) == 1 and dense_of(fff_lib, xw[:n - 1], ww, ww, d) == 0
+    big = torch.zeros(139265, 768, dtype=torch.bfloat16, device=DEV)
     w10 = w[:, :2047].contiguous()
-    for n, d11, d10, d7 in ((81920, 1, 1, 1), (81921, 0, 0, 0), (98303, 0, 0, 0), (98304, 1, 0, 1), (131072, 1, 0, 1)):
+    for n, d11, d10, d7 in ((69632, 1, 1, 1), (69633, 0, 0, 0), (98303, 0, 0, 0), (98304, 0, 0, 1), (114687, 0, 0, 1),
+                            (114688, 1, 0, 1), (139264, 1, 0, 1), (139265, 0, 0, 1)):
         assert (dense_of(fff_lib, big[:n], w, w, 11), dense_of(fff_lib, big[:n], w10, w10, 10),
                 dense_of(fff_lib, big[:n], w7, w7, 7)) == (d11, d10, d7), n
     w12 = torch.zeros(1, 8191, 768, dtype=torch.bfloat16, device=DEV)
@@ -1050,7 +1059,7 @@ def test_tiled_dense_output_modes(fff_lib, D, B, out):
 
 
 def test_tiled_dense_token_chunks(fff_lib):
-    """More tokens than one pair of passes takes (98304): chunks of equal size, every row written."""
+    """More tokens than one pair of passes takes (69632): chunks of equal size, every row written."""
     L = layer(320, 100003, 768, 6, 1, "bf16", "bf16")
     check_layer(fff_lib, "tiled dense chunks", L, 6, 1, "bf16", mode="tiled")
 
@@ -1068,6 +1077,22 @@ def test_tiled_dense_skewed_routing_deterministic(fff_lib):
     assert np.array_equal(a["y"], b["y"]) and np.array_equal(a["nodes"], b["nodes"])
     c = run_fff(fff_lib, dict(L, x=np.ascontiguousarray(x[1001:51001])), D, 1, "bf16", mode="tiled")
     assert np.array_equal(a["y"][1001:51001], c["y"]) and np.array_equal(a["logits"][1001:51001], c["logits"])
+
+
+@pytest.mark.parametrize("B", [8207, 69632])
+def test_tiled_dense_group_sizes(fff_lib, B):
+    """Groups of every size in one batch, from none to most of it (the bound on a workgroup's tokens follows
+    them): each token's row is the one it has in a batch of uniform routing."""
+    D = 7 if B < 49152 else 11
+    wi, wo = synth.make_weights(335, 768, D, 1, "bf16")
+    x = np.concatenate([synth.make_clustered_x(335, B - B // 3, 768, "bf16", n_centres=2), synth.make_x(336, B // 3, 768, "bf16")])
+    L = {"x": x, "w_in": wi, "w_out": wo}
+    check_layer(fff_lib, f"tiled dense groups B={B}", L, D, 1, "bf16", mode="tiled")
+    got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled")
+    uniform = np.concatenate([synth.make_x(337, B - 1000, 768, "bf16"), x[:500], x[-500:]])
+    ref = run_fff(fff_lib, dict(L, x=uniform), D, 1, "bf16", mode="tiled")
+    for k in ("y", "nodes", "logits"):
+        assert np.array_equal(np.concatenate([got[k][:500], got[k][-500:]]), ref[k][-1000:]), k
 
 
 @pytest.mark.parametrize("D,B", [(5, 4300), (11, 50000)])
