@@ -156,7 +156,7 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_wide_token_kernel(BwdParams p, 
             const bool ok = valid && leaf_ok(leaf, D);
             const uint32_t leaf1 = uint32_t(ok ? leaf : int32_t(L - 1)) + 1;
             if (sl == 0) {
-                if (ok && p.need_dw) atomicAdd(&p.counts[t * L + (int64_t(leaf1) - L)], 1);
+                if (ok && p.need_dw && !p.leaf_sums) atomicAdd(&p.counts[t * L + (int64_t(leaf1) - L)], 1);
                 if (valid && !ok && p.bad) atomicAdd(p.bad, 1);
             }
             const uint32_t tree = uint32_t(t) * uint32_t(p.n_nodes) * rowb;
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_base_kernel(BwdParams p, int se
 }
 
 // bwd_leafsum_kernel (one wave per (tree, leaf)): the leaf's token count, the
-// sum of its chunk counts (the fused path counts leaves here, not in a token
+// sum of its chunk counts (p.leaf_sums: leaves are counted here, not in a token
 // kernel).
 __global__ __launch_bounds__(BWD_BLOCK) void bwd_leafsum_kernel(BwdParams p) {
     const int64_t L = int64_t(1) << p.depth;
@@ -1885,6 +1885,8 @@ const BwdVariant kBwdVariants[] = {
     FFF_BWD(1024, false, 32, 8), FFF_BWD(4096, true, 64, 8), FFF_BWD(4096, false, 64, 16),
 };
 
+constexpr int64_t LEAF_SUM_TOKENS = 64;  // tokens per leaf from which counts are sums of the chunks' counts
+
 // The vector-row token kernel for p's width (kernel null where it does not apply).
 struct BwdWide {
     const void* kernel = nullptr;
@@ -2011,7 +2013,7 @@ static hipError_t launch_wsum(BwdParams& p, int k, hipStream_t stream) {
 }
 
 // The stable placement in leaf order (rank, [leaf sums], scan, base, place).
-static hipError_t launch_sort(BwdParams& p, bool count_leaves, const int64_t cap, hipStream_t stream) {
+static hipError_t launch_sort(BwdParams& p, const int64_t cap, hipStream_t stream) {
     void* args[] = {&p};
     const int64_t bins = (int64_t(1) << p.depth) * p.n_trees;
     hipError_t e =
@@ -2021,15 +2023,15 @@ static hipError_t launch_sort(BwdParams& p, bool count_leaves, const int64_t cap
             : hipLaunchKernel(reinterpret_cast<const void*>(&bwd_rank_kernel), dim3(unsigned(p.chunks), p.n_trees),
                               dim3(RANK_BLOCK), args, size_t(p.chunk) * sizeof(int32_t), stream);
     if (e != hipSuccess) return e;
-    if (count_leaves) {
+    if (p.leaf_sums) {
         e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_leafsum_kernel),
                             dim3(unsigned((bins + BWD_BLOCK / 64 - 1) / (BWD_BLOCK / 64))), dim3(BWD_BLOCK), args, 0,
                             stream);
         if (e != hipSuccess) return e;
     }
-    // the fused path (leaf counts from bwd_leafsum_kernel, one tree) with few leaves: the base
+    // the fused path (one tree, no use for the total) with few leaves: the base
     // kernel finds each leaf's start itself; otherwise the scan kernel (which also gives the total)
-    int self_scan = count_leaves && p.n_trees == 1 && bins <= BASE_SELF_SCAN_LEAVES;
+    int self_scan = p.fused && bins <= BASE_SELF_SCAN_LEAVES;
     if (!self_scan) {
         e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_scan_kernel), dim3(p.n_trees), dim3(SCAN_BLOCK), args,
                             0, stream);
@@ -2069,7 +2071,8 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
     p.fused = p.need_dw && p.w_bf16 && p.n_trees == 1 && wtile_shape(p.depth, p.hidden) && p.hidden <= 1024;
     if (p.fused) {
         p.fused16 = p.x_bf16 && p.dy_bf16 && p.hidden >= 4 * F16_COLS && p.hidden <= F16_COLS * F16_WAVES_MAX;
-        hipError_t e = launch_sort(p, true, cap, stream);
+        p.leaf_sums = 1;
+        hipError_t e = launch_sort(p, cap, stream);
         if (e != hipSuccess) return e;
         const int k = wtile_k(p.depth);
         int sub = p.depth - k;
@@ -2093,7 +2096,12 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
         return launch_wsum(p, k, stream);
     }
     void* args[] = {&p};
-    if (p.need_dw) {  // zero the leaf counts (a fill kernel: no memset nodes)
+    // Leaf counts of the vector-row kernel: many tokens per leaf meet on few counters, which then bound it, and
+    // harder the faster the kernel is (64 trees of depth 0, hidden 128, 16384 tokens: token kernel 7479 us, a wave
+    // per token 5632).  Sums of the chunks' counts instead (hidden 100, 8000 tokens: a backward 3997 -> 393 us;
+    // a wave per token 3747).
+    p.leaf_sums = p.need_dw && wide.kernel && p.n_tokens >= (LEAF_SUM_TOKENS << p.depth);
+    if (p.need_dw && !p.leaf_sums) {  // zero the leaf counts (a fill kernel: no memset nodes)
         const int64_t bins = (int64_t(1) << p.depth) * p.n_trees;
         float* a = nullptr;
         int64_t na = 0;
@@ -2131,7 +2139,7 @@ hipError_t run_backward(BwdParams p, const DeviceInfo& dev, hipStream_t stream, 
         if (e != hipSuccess) return e;
     }
     if (!p.need_dw) return hipSuccess;
-    hipError_t e = launch_sort(p, false, cap, stream);
+    hipError_t e = launch_sort(p, cap, stream);
     if (e != hipSuccess) return e;
     if (wtile_shape(p.depth, p.hidden)) {  // weight sums on MFMA, leaf by leaf
         const int k = wtile_k(p.depth, p.n_trees, p.hidden);

@@ -96,6 +96,7 @@ struct BwdParams {
     int64_t chunks;          // token chunks of the stable placement
     int32_t chunk;           // tokens per chunk
     int32_t fused;           // the fused leaf-tiled path runs (no token kernel)
+    int32_t leaf_sums;       // leaf counts are sums of the chunks' counts, not counted by a token kernel
     int32_t fused16;         // ... with bf16 x and dy: coef holds (act(l), act'(l))
     float* part;             // [T, pieces, D+1, 2 slots, 2 matrices, H] run sums that cross pieces
     char* junk;              // BWD_JUNK_BYTES the fused kernel sends the stores of absent dx rows to
