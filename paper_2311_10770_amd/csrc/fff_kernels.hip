@@ -1409,6 +1409,19 @@ static bool plan_walk(const Params& p, const Variant& v, int lds_levels_req, con
     return true;
 }
 
+// Many trees of a single node over rows of at most an element per lane, and tokens that leave the chip
+// unfilled: the vector-row kernel's chain is a W_in row, then the W_out row, tree after tree, where a wave per
+// token takes all the logits first and then independent rows.  Times of the vector rows over those of the
+// wave per token, hidden 8 to 64: x widened with bf16 W, 16 trees 1.07-1.18 up to 2048 tokens, 0.99-1.01 at
+// 3000, 64 trees 1.19-1.38 and 1.09-1.23 (0.95-1.08 at 4096, 0.62 at 8192); fp32 W, 64 trees 1.02-1.16 up to
+// 2048, 0.90-1.01 at 3000, 32 trees 0.85-1.02.  bf16 x and W 0.73-1.03; hidden 128 0.63-0.95; with a descent
+// 0.27-1.02.
+static bool narrow_roots(const Params& p, int cu_count) {
+    if (p.depth != 0 || p.hidden > 64 || (p.w_bf16 && p.x_bf16 && !p.norm)) return false;
+    return p.w_bf16 ? p.n_trees >= 16 && p.n_tokens <= 16 * int64_t(cu_count)
+                    : p.n_trees >= 64 && p.n_tokens <= 8 * int64_t(cu_count);
+}
+
 int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_req, size_t workspace_bytes,
                  const DeviceInfo& dev, Plan* plan, bool masked_ok) {
     *plan = Plan{};
@@ -1590,7 +1603,7 @@ int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_
     if (pairs > GENERIC_MAX_PAIRS) return ST_UNSUPPORTED;
     plan->kind = KIND_GENERIC;
     WidePlan wide;
-    if (wide_plan(p, &wide)) {
+    if (!narrow_roots(p, dev.cu_count) && wide_plan(p, &wide)) {
         plan->wide_vecs = wide.rowv;
         plan->lanes = wide.lanes;
         plan->name = "vector rows";

@@ -1158,3 +1158,21 @@ def test_generic_vector_rows_block(fff_lib, xd, wd, yd, H):
     got = run_fff(fff_lib, L, D, 1, yd, mode="generic", out="accumulate", y_init=y0)
     ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
     parity.assert_parity(L["x"], L["w_in"], L["w_out"], D, 1, ref, got["y"], got["nodes"], tol=tol_for(wd, yd), base_dev=y0)
+
+
+@pytest.mark.parametrize("xd,wd,H,T", [("f32", "bf16", 8, 16), ("f32", "bf16", 64, 64), ("bf16", "f32", 4, 64),
+                                       ("bf16", "f32", 64, 300)])
+def test_generic_single_nodes(fff_lib, xd, wd, H, T):
+    """Many trees of one node over narrow rows: a wave per token where the tokens leave the chip unfilled, the
+    vector rows for one tree less, wider rows or more tokens; the same results."""
+    L = layer(420 + H, 33, H, 0, T, xd, wd)
+    x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
+    kw = dict(mode="generic", y_dtype=torch.float32)
+    assert "wave per token" in fff_lib.describe(x, wi, wo, 0, T, **kw)
+    least = 16 if wd == "bf16" else 64
+    assert "vector rows" in fff_lib.describe(x, wi[:least - 1].contiguous(), wo[:least - 1].contiguous(), 0, least - 1, **kw)
+    many = torch.zeros((8192, H), dtype=x.dtype, device=DEV)
+    assert "vector rows" in fff_lib.describe(many, wi, wo, 0, T, **kw)
+    check_layer(fff_lib, f"single nodes {xd}/{wd} H={H} T={T}", L, 0, T, "f32", mode="generic")
+    few = {k: L[k][:least - 1].copy() for k in ("w_in", "w_out")}
+    check_layer(fff_lib, f"single nodes {xd}/{wd} H={H} T={least - 1}", dict(L, **few), 0, least - 1, "f32", mode="generic")
