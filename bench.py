@@ -169,6 +169,8 @@ def main():
         dwo = torch.empty_like(dwi)
         fused = (w.n_trees == 1 and w.w_dtype == "bf16" and w.depth <= 15 and w.hidden % 128 == 0
                  and w.hidden <= 1024)
+        fused_kernel = ("bwd_fused16_kernel" if w.x_dtype == w.y_dtype == "bf16" and 256 <= w.hidden <= 768 else
+                        "bwd_fused_kernel")
         plan = ("backward: stable sort by leaf (rank, leaf sums, base, place) + fused leaf-tiled kernel "
                 "(da, dx, dW on MFMA per 16-token tile) + sums of the rows above the subtrees" if fused else
                 "backward: token kernel + stable sort by leaf + weight kernel + fix-up sums")
@@ -238,6 +240,8 @@ def main():
             log(f"{tpath.name} was taken on other kernel sources: traffic unreported")
     if "grouped<" in plan:
         kernels = "walk_kernel + emit_kernel"
+    elif "tiled<" in plan and "dense=1" in plan:
+        kernels = ("" if "top_levels=0" in plan else "dense_top_kernel + ") + "dense_sub_kernel"
     elif "tiled<" in plan:
         kernels = "fill_i32_kernel + walk_kernel + tile_kernel"
     else:
@@ -251,7 +255,7 @@ def main():
         per_tok = w.hidden * (2 * sz[w.x_dtype] + sz[w.y_dtype]) + 4 * w.n_trees * (w.depth + 2)
         bwd_bytes = B * per_tok + w.n_trees * w.nodes * w.hidden * 2 * (sz[w.w_dtype] + 4)
         kernels = ("bwd_rank_wave_kernel + bwd_leafsum_kernel + bwd_base_kernel (+ bwd_scan_kernel past 4096 "
-                   "leaves) + bwd_place_kernel + bwd_fused_kernel + bwd_wsum_kernel" if fused else
+                   f"leaves) + bwd_place_kernel + {fused_kernel} + bwd_wsum_kernel" if fused else
                    "bwd_token_kernel + sort kernels + bwd_wtile_kernel / bwd_piece_kernel + fix-up")
         bach = bwd_bytes / (ms / 1e3) / 1e9
         out["roofline"] = {"bound": "hbm", "achieved": bach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -310,8 +314,9 @@ def main():
         out["valu_only"] = {"mode": vmode, "ms_per_step": vms, "tokens_per_s": B / (vms / 1e3),
                             "roofline_frac": w.compulsory_bytes(B) / (vms / 1e3) / 1e9 / HBM_PEAK_GBS,
                             "plan": fff.describe(x, wi, wo, w.depth, w.n_trees, y, **vkw, **layer_kw(0)),
-                            "why": "the default plan accumulates the outputs of tokens that share a leaf on "
-                                   "MFMA; this is the layer on the vector ALU alone"}
+                            "why": "the default plan forms products of many tokens on MFMA (tiled: the outputs of "
+                                   "a leaf's tokens, or the logits and outputs of whole subtrees; masked: all "
+                                   "logits and outputs); this is the layer on the vector ALU alone"}
         log(f"vector-ALU plan ({vmode}): {vms * 1e3:.1f} us/step, {B / (vms / 1e3) / 1e6:.1f} M tok/s")
 
     if not args.no_dense and not args.backward:

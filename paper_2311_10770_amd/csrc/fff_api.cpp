@@ -527,15 +527,17 @@ namespace {
 void format_plan(const fff::Plan& plan, const char* prefix, char* buf, size_t len) {
     if (!buf || !len) return;
     static const char* kinds[] = {"none", "descent", "generic", "grouped", "stack", "tiled", "masked", "subtree"};
-    int n = std::snprintf(buf, len, "%s%s<%s> lanes_per_token=%d lds_levels=%d", prefix, kinds[plan.kind],
-                          plan.name, plan.lanes, plan.lds_levels);
+    int n = plan.dense ? std::snprintf(buf, len, "%s%s<%s> dense=1 top_levels=%d", prefix, kinds[plan.kind], plan.name,
+                                       plan.split_level)
+                       : std::snprintf(buf, len, "%s%s<%s> lanes_per_token=%d lds_levels=%d", prefix, kinds[plan.kind],
+                                       plan.name, plan.lanes, plan.lds_levels);
     if (plan.kind == fff::KIND_SUBTREE && n > 0 && size_t(n) < len)
         n += std::snprintf(buf + n, len - n, " levels_per_step=%d", plan.split_level);
-    if ((plan.kind == fff::KIND_GROUPED || plan.kind == fff::KIND_TILED) && n > 0 && size_t(n) < len)
+    if ((plan.kind == fff::KIND_GROUPED || plan.kind == fff::KIND_TILED) && !plan.dense && n > 0 && size_t(n) < len)
         n += std::snprintf(buf + n, len - n, " emit_lds_levels=%d split_level=%d emit_lanes=%d walk_tree_per_xcd=%d",
                            plan.emit_lds_levels, plan.split_level, plan.emit_lanes, plan.walk_affine);
-    if (plan.kind == fff::KIND_TILED && n > 0 && size_t(n) < len)
-        n += std::snprintf(buf + n, len - n, " leaf_pairs=%d dense=%d", plan.tile_pair, plan.dense);
+    if (plan.kind == fff::KIND_TILED && !plan.dense && n > 0 && size_t(n) < len)
+        n += std::snprintf(buf + n, len - n, " leaf_pairs=%d dense=0", plan.tile_pair);
     for (int i = 0; i < plan.n_launch && n > 0 && size_t(n) < len; ++i)
         n += std::snprintf(buf + n, len - n, " | launch%d grid=%d block=%d lds_bytes=%zu", i, plan.launch[i].grid,
                            plan.launch[i].block, plan.launch[i].lds_bytes);

@@ -10,11 +10,11 @@
 //     order; each token descends through its row of logits in LDS, and leaves
 //     its activations, its node at level s (the group) and, per workgroup, how
 //     many of its tokens went to each group;
-//   subtree pass (dense_sub_kernel): a workgroup takes up to 128 tokens of one
-//     group (found from those counts, in token order: no atomics), gathers their
-//     x rows, does the same for levels s .. D of the group's subtree, and then
+//   subtree pass (dense_sub_kernel): a workgroup takes up to DS_TOK (384) tokens
+//     of one group (found from those counts, in token order: no atomics), gathers
+//     their x rows, does the same for levels s .. D of the group's subtree, and then
 //     forms the tokens' whole output
-//         Y[128, H] = A[128, s + 63] W_out[s ancestors and 63 subtree nodes, H],
+//         Y[tokens, H] = A[tokens, s + 63] W_out[s ancestors and 63 subtree nodes, H],
 //     A holding a token's activation at its visited nodes and zeros elsewhere.
 // With D < 6 there is no top pass: the one group is the whole tree.
 //
@@ -723,22 +723,46 @@ static int dense_item(int64_t n_tokens, int cu_count) {
     return int(std::max<int64_t>(item, DN_ITEM_MIN));
 }
 
+// Equal chunks of at most DN_CHUNK tokens.
+int64_t dense_chunk(int64_t n_tokens) {
+    const int64_t chunks = std::max<int64_t>(1, (n_tokens + DN_CHUNK - 1) / DN_CHUNK);
+    return (n_tokens + chunks - 1) / chunks;
+}
+
+int dense_launches(const Params& p, int64_t n_tokens, int cu_count, Launch* L) {
+    const int s = dense_top_levels(p.depth), sub = p.depth + 1 - s;
+    int n = 0;
+    if (s) {
+        L[n].kernel = s > 5 ? reinterpret_cast<const void*>(&dense_top_kernel<4>) : reinterpret_cast<const void*>(&dense_top_kernel<2>);
+        L[n].grid = int((n_tokens + DT_TOK - 1) / DT_TOK);
+        L[n].block = 64 * DT_WAVES;
+        L[n++].lds_bytes = s > 5 ? dense_top_lds<4>() : dense_top_lds<2>();
+    }
+    const bool src = p.out_mode != OUT_STORE;
+    L[n].kernel = sub > 5 ? (src ? reinterpret_cast<const void*>(&dense_sub_kernel<4, true>)
+                                 : reinterpret_cast<const void*>(&dense_sub_kernel<4, false>))
+                          : (src ? reinterpret_cast<const void*>(&dense_sub_kernel<2, true>)
+                                 : reinterpret_cast<const void*>(&dense_sub_kernel<2, false>));
+    L[n].block = DS_THREADS;
+    L[n].lds_bytes = sub > 5 ? DSub<4>::lds(p.hidden) : DSub<2>::lds(p.hidden);
+    if (s) {
+        // at most one item per whole `most` tokens and one partly filled per group: a round of them, or with
+        // the bound at its least or its most
+        const int64_t groups = int64_t(1) << s;
+        const int64_t items = std::min(n_tokens / DN_ITEM_MIN + groups, std::max<int64_t>(cu_count, n_tokens / DS_TOK + groups));
+        L[n++].grid = int((items + XCDS - 1) / XCDS * XCDS);
+    } else {
+        const int item = dense_item(n_tokens, cu_count);
+        L[n++].grid = int((n_tokens + item - 1) / item);
+    }
+    return n;
+}
+
 hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t stream) {
     const int levels = p.depth + 1, s = dense_top_levels(p.depth), sub = levels - s;
-    const void* const top = s > 5 ? reinterpret_cast<const void*>(&dense_top_kernel<4>)
-                                  : reinterpret_cast<const void*>(&dense_top_kernel<2>);
-    const size_t top_lds = s > 5 ? dense_top_lds<4>() : dense_top_lds<2>();
-    const bool src = p.out_mode != OUT_STORE;
-    const void* const subk = sub > 5 ? (src ? reinterpret_cast<const void*>(&dense_sub_kernel<4, true>)
-                                            : reinterpret_cast<const void*>(&dense_sub_kernel<4, false>))
-                                     : (src ? reinterpret_cast<const void*>(&dense_sub_kernel<2, true>)
-                                            : reinterpret_cast<const void*>(&dense_sub_kernel<2, false>));
-    const size_t sub_lds = sub > 5 ? DSub<4>::lds(p.hidden) : DSub<2>::lds(p.hidden);
     const int64_t H = p.hidden;
-    const int cus = cu_count > 0 ? cu_count : 256;
     // pairs of passes over equal chunks
-    const int64_t chunks = (p.n_tokens + DN_CHUNK - 1) / DN_CHUNK;
-    const int64_t chunk = (p.n_tokens + chunks - 1) / chunks;
+    const int64_t chunk = dense_chunk(p.n_tokens);
     for (int64_t c0 = 0; c0 < p.n_tokens; c0 += chunk) {
         Params c = p;
         c.n_tokens = std::min(chunk, p.n_tokens - c0);
@@ -761,20 +785,16 @@ hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t
         a.hist_ld = int32_t((wgs + 15) / 16 * 16);
         a.s = s;
         a.levels = sub;
-        a.item = s ? DN_ITEM_MIN : dense_item(c.n_tokens, cus);
-        a.round = cus;
+        a.item = s ? DN_ITEM_MIN : dense_item(c.n_tokens, cu_count);
+        a.round = cu_count;
         void* args[] = {&c, &a};
-        if (s) {
-            const hipError_t e = hipLaunchKernel(top, dim3(unsigned(wgs)), dim3(64 * DT_WAVES), args, top_lds, stream);
+        Launch L[2];
+        const int n = dense_launches(c, c.n_tokens, cu_count, L);
+        for (int i = 0; i < n; ++i) {
+            const hipError_t e = hipLaunchKernel(L[i].kernel, dim3(unsigned(L[i].grid)), dim3(unsigned(L[i].block)), args,
+                                                 L[i].lds_bytes, stream);
             if (e != hipSuccess) return e;
         }
-        // at most one item per whole `most` tokens and one partly filled per group: a.round of them, or
-        // with the bound at its least or its most
-        const int64_t groups = int64_t(1) << s;
-        const int64_t items = std::min(c.n_tokens / a.item + groups, std::max<int64_t>(a.round, c.n_tokens / DS_TOK + groups));
-        const int64_t grid = s ? (items + XCDS - 1) / XCDS * XCDS : (c.n_tokens + a.item - 1) / a.item;
-        const hipError_t e = hipLaunchKernel(subk, dim3(unsigned(grid)), dim3(DS_THREADS), args, sub_lds, stream);
-        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -135,18 +135,19 @@ struct Launch {
 
 struct Plan {
     int kind = KIND_NONE;
-    Launch launch[3];              // descent/generic: [0]; grouped: walk, emit; tiled: fill, walk, tiles (one per tree)
+    Launch launch[3];              // descent/generic: [0]; grouped: walk, emit; tiled: fill, walk, tiles (one per tree),
+                                   // or (dense) the top pass, where there is one, and the subtree pass of a chunk
     int n_launch = 0;
     int lanes = 0;                 // lanes per token
     int emit_lanes = 0;            // lanes per token of the grouped emit
     int lds_levels = 0;            // descent, generic, grouped walk
     int emit_lds_levels = 0;       // grouped emit
-    int split_level = 0;           // grouped mode
+    int split_level = 0;           // grouped mode; dense: levels of the top pass
     int walk_affine = 0;           // grouped / tiled: one tree per walk workgroup, by XCD
     int tile_pair = 0;             // tiled: a tile workgroup per pair of sibling leaves
     int dense = 0;                 // tiled: subtrees as dense products (fff_dense.hip) instead of walk and leaf tiles
     int wide_vecs = 0;             // generic, rows of whole 16-byte vectors: vectors per row
-    int cu_count = 0;              // masked: compute units, for the products' tile choice
+    int cu_count = 0;              // masked, dense: compute units
     const char* name = "";
 };
 
@@ -185,10 +186,13 @@ size_t grouped_workspace_bytes(int64_t n_tokens, int32_t depth, int32_t n_trees,
 // Tiled mode scratch (grouped scratch plus the leaf buckets); 0 when the shape has no tiled mode.
 size_t tiled_workspace_bytes(int64_t n_tokens, int32_t depth, int32_t n_trees, int32_t hidden);
 // The dense form of tiled mode (fff_dense.hip): whether a validated tiled request has it, the levels
-// of its top pass (0: none), its scratch (less than the leaf buckets') and the launch.
+// of its top pass (0: none), its scratch (less than the leaf buckets'), the launches of one chunk of
+// tokens (of a whole batch: its first chunk) and the run.
 bool dense_shape(const Params& p);
 int dense_top_levels(int32_t depth);
+int64_t dense_chunk(int64_t n_tokens);
 size_t dense_workspace_bytes(int64_t n_tokens);
+int dense_launches(const Params& p, int64_t n_tokens, int cu_count, Launch* L);
 hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t stream);
 // GENERIC for rows of whole 16-byte vectors (fff_wide.hip): the kernel for p's row length and types;
 // false where it does not apply.

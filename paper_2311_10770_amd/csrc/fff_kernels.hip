@@ -1539,7 +1539,11 @@ int plan_forward(const Params& p, int mode, int lds_levels_req, int split_level_
         plan->tile_pair = tile_pairs(p) ? 1 : 0;
         plan->dense = lds_levels_req == 0 && dense_plan(p);  // a request for LDS levels is the walk's to grant or refuse
         plan->cu_count = dev.cu_count;
-        if (plan->dense) return ST_OK;
+        if (plan->dense) {
+            plan->split_level = dense_top_levels(p.depth);
+            plan->n_launch = dense_launches(p, dense_chunk(p.n_tokens), dev.cu_count, plan->launch);
+            return ST_OK;
+        }
         const int64_t leaves = int64_t(1) << p.depth;
         Launch& F = plan->launch[plan->n_launch++];
         F.kernel = reinterpret_cast<const void*>(&fill_i32_kernel);

@@ -25,11 +25,11 @@ def kernel_source_hash(backward: bool = False) -> str:
     """Hash of the sources the forward (or backward) kernels are compiled from: counter figures
     taken on them are void once these change."""
     h = hashlib.sha256()
-    main = ("fff_backward.hip",) if backward else ("fff_kernels.hip", "fff_dense.hip")
-    for name in (*main, "fff_common.hpp", "fff_device.hpp", "fff_internal.hpp"):
-        p = PKG / "csrc" / name
-        if p.exists():
-            h.update(p.read_bytes())
+    csrc = PKG / "csrc"
+    kernels = [csrc / "fff_backward.hip"] if backward else [
+        p for p in csrc.glob("fff_*.hip") if p.name != "fff_backward.hip"]
+    for p in sorted(kernels) + sorted(csrc.glob("fff_*.hpp")):
+        h.update(p.read_bytes())
     return h.hexdigest()[:16]
 
 

@@ -988,7 +988,9 @@ def test_tiled_dense(fff_lib, H, D, B):
     """The dense form against the oracle: ragged last tiles and workgroups, every split of the levels."""
     L = layer(300 + D, B, H, D, 1, "bf16", "bf16")
     x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
-    assert dense_of(fff_lib, x, wi, wo, D) == 1
+    plan = fff_lib.describe(x, wi, wo, D, 1, mode="tiled")  # the passes that run: a subtree pass, after a top pass
+    assert "dense=1" in plan and plan.count("launch") == (1 if D == 5 else 2) and "emit" not in plan, plan
+    assert f"top_levels={ {5: 0, 6: 3, 7: 4, 8: 4, 9: 5}.get(D, 6)} " in plan, plan
     check_layer(fff_lib, f"tiled dense H={H} B={B} D={D}", L, D, 1, "bf16", mode="tiled")
 
 
