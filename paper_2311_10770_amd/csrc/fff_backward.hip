@@ -171,7 +171,7 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_wide_token_kernel(BwdParams p, 
             };
             auto level = [&](int l, int b) {
                 const float logit = ok ? lg[b] : 0.0f;
-                const float da = group_sum<LANES>(gy.dot(ro[b]));
+                const float da = group_sum<LANES>(wide_dot<NV, false, WBF>(gy, ro[b]));
                 const float dl = ok ? da * activation_grad(logit, p.act) : 0.0f;
                 axpy<NV, WBF>(acc, dl, ri[b]);
                 if (ok && sl == 0 && p.need_dw) p.coef[rec0 + l] = make_float2(activation(logit, p.act), dl);
@@ -1676,11 +1676,14 @@ __global__ __launch_bounds__(64 * F16_WAVES_MAX) void bwd_fused16_kernel(BwdPara
                     issue(Pn, mn, buf ^ 1);
                 }
                 __syncthreads();
-                // 2. a and dl of the tile's (token, level) pairs, the partials added in wave order
+                // 2. a and dl of the tile's (token, level) pairs, the partials of every second wave added in order
                 if (wave < 4) {
-                    float d = 0.0f;
-                    for (int w = 0; w < waves; ++w) d += red[w][at][alv];
-                    const float dl = at < m && alv <= D ? d * cf.y : 0.0f;  // cf is zero where absent
+                    float d0 = 0.0f, d1 = 0.0f;  // an even number of waves
+                    for (int w = 0; w < waves; w += 2) {
+                        d0 += red[w][at][alv];
+                        d1 += red[w + 1][at][alv];
+                    }
+                    const float dl = at < m && alv <= D ? (d0 + d1) * cf.y : 0.0f;  // cf is zero where absent
                     uint16_t dp[3], ap[3];
                     split3(dl, dp);
                     split3(cf.x, ap);

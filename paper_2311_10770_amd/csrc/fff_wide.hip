@@ -103,7 +103,7 @@ __global__ __launch_bounds__(WIDE_BLOCK) void wide_kernel(Params p, int rowv) {
             lv.clear();
             uint32_t n = 0;
             auto visit = [&](int l, const uint4* w) {
-                const float logit = group_sum<LANES>(xr.dot(w));
+                const float logit = group_sum<LANES>(wide_dot<NV, XDOT, WBF>(xr, w));
                 lv.park(l, sl, logit);
                 if (l < D) n = 2 * n + 1 + (logit > 0.0f ? 1u : 0u);
             };

@@ -101,6 +101,40 @@ __device__ __forceinline__ void wide_store(void* y, bool ybf, const void* src, b
     }
 }
 
+// This lane's part of the dot product of a row in registers (x, in the layout of Shape<LANES, NV, XDOT, WBF>)
+// with a W row: a sum per four elements (eight bf16 x), the sums added in pairs.  One chain over all of a
+// lane's elements (up to 64) loses against a wave per token, whose lanes hold one in 64: hidden 512, fp32 x
+// with bf16 W, logits off by 1.16e-7 (relative, 2-norm) so, 8.5e-8 there, 8.2e-8 here.
+template <int NV, bool XDOT, bool WBF, class X>
+__device__ __forceinline__ float wide_dot(const X& x, const uint4* w) {
+    float s[NV], zero = 0.0f;
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+        float h[2] = {zero, zero};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t u = word(w[c], j);
+            if constexpr (XDOT) {
+                h[0] = dot2_bf16(word(x.v[c], j), u, h[0]);
+            } else if constexpr (WBF) {
+                h[j / 2] = __builtin_fmaf(x.f[c * 8 + 2 * j], bf16_lo(u), h[j / 2]);
+                h[j / 2] = __builtin_fmaf(x.f[c * 8 + 2 * j + 1], bf16_hi(u), h[j / 2]);
+            } else {
+                h[0] = __builtin_fmaf(x.f[c * 4 + j], __uint_as_float(u), h[0]);
+            }
+        }
+        s[c] = WBF && !XDOT ? h[0] + h[1] : h[0];
+        // the sums in order, each while the vectors after it arrive (interleaved, most wait for the last one):
+        // the next one starts from a zero that this one's end hands out
+        asm volatile("" : "+v"(s[c]), "+v"(zero));
+    }
+#pragma unroll
+    for (int d = 1; d < NV; d *= 2)
+#pragma unroll
+        for (int c = 0; c + d < NV; c += 2 * d) s[c] += s[c + d];
+    return s[0];
+}
+
 // The (LANES, NV) classes: f(lanes, nv), integral constants, for the smallest that holds rowv vectors
 // (at most WIDE_MAX_VECS).  Sixteen lanes up to six vectors each (heavy layouts, 16 fp32 registers per
 // vector and lane besides the row: up to four), then as few lanes as keep two waves per SIMD.
