@@ -78,17 +78,16 @@ typedef enum { FFF_ACT_GELU_ERF = 0, FFF_ACT_GELU_TANH = 1, FFF_ACT_IDENTITY = 2
  * GENERIC: any hidden size; rows of whole 16-byte vectors as a fused descent
  * with the row length as a run-time value, other rows a wave per token.
  * TILED (large batches of bf16 x, W and y through one tree of depth at most 11,
- * hidden a multiple of 128 up to 1024, take the tree's subtrees as dense
- * products on MFMA instead of what follows):
- * 1..16 trees, depth 5..15, hidden a multiple of 128: the walk drops
+ * hidden 768 or 1024, without logits_out and a request for lds_levels, take the
+ * tree's subtrees as dense products on MFMA instead of what follows):
+ * 1..16 trees, depth 5..15, hidden 768, 1024 or 4096: the walk drops
  * each token into a bucket of its leaf in every tree, and the output rows of up
  * to 16 tokens that share a leaf (hence all D+1 nodes) are accumulated as one
  * dense product on MFMA, one launch per tree in tree order, each adding its
  * tree to the running sum (fp32 y in place; for a bf16 y an fp32 row of the
  * workspace, rounded once by the last tree): fp32 MFMA for fp32 weights; for bf16 weights bf16 MFMA on the
  * activations split into bf16 parts (three parts: fp32 working accuracy; two,
- * relative error about 2^-17, when y is bf16 and either stored or the residual
- * of bf16 x).  Below 16 tokens per leaf on average (depth <= 14) one
+ * relative error about 2^-17, when y is bf16).  Below 16 tokens per leaf on average (depth <= 14) one
  * workgroup takes a pair of sibling leaves: their tokens share the rows of
  * levels 0..D-1 and fill one list of tiles, with the two leaves' rows as two
  * extra rows of the product (each token's leaf activation on its own leaf's
@@ -199,7 +198,7 @@ typedef struct {
     int32_t act;                       /* fff_act */
     int32_t mode;                      /* fff_mode */
     int32_t out_mode;                  /* fff_out */
-    int32_t lds_levels;   /* top tree levels cached in LDS (DESCENT); 0 = default choice,
+    int32_t lds_levels;   /* top tree levels cached in LDS (DESCENT, GROUPED, TILED); 0 = default choice,
                              -1 = none, k > 0 = exactly k (FFF_ERR_UNSUPPORTED if too big) */
     int32_t split_level;  /* GROUPED: group tokens by their tree-0 node at this level (3..depth);
                              0 = default (min(depth, 5) for one tree, else none);

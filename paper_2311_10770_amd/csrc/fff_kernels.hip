@@ -1357,17 +1357,18 @@ static bool tile_pairs(const Params& p) {
 }
 
 // Subtrees as dense products (fff_dense.hip), where that beats the walk and the leaf tiles: at depths 10
-// and 11 from 49152 tokens, shallower from 64 per leaf (96 at hidden 1024) and enough for the CUs.  Up to
+// and 11 from 49152 tokens, shallower from 64 per leaf (96 at hidden 1024) and enough for the CUs (not where
+// the logits are recorded: they are less exact there).  Up to
 // 69632 the subtree workgroups are one round whatever the routing; past that two rounds, at depth 11 of at
 // least 57344 each.  bf16, buffers rotating, times over those of the walk and the leaf tiles, the range
 // over four sets of weights:
-//   depth 11, hidden 768, 49152 / 57344 / 65536 / 69632 / 73728 tokens: stored 0.93 / 0.92-0.94 /
-//     0.93-0.95 / 0.97-0.98 / 1.00-1.01, residual with records 0.99-1.00 / 0.93-0.95 / 0.92-0.93 /
-//     0.93-0.95 / 0.95; hidden 1024, 0.81-0.95 and 0.88-0.95; accumulating 0.85-0.92
-//   two rounds, 98304 / 114688 / 131072: 0.98-1.00 / 0.94-0.95 / 0.93-0.94 stored, 1.00-1.02 / 0.94-0.96 /
-//     0.93-0.94 residual, 1.05 / - / 1.00 accumulating with records; three 0.97-1.07 (163840 to 229376)
+//   depth 11, hidden 768, 49152 / 57344 / 65536 / 69632 / 73728 tokens: stored 0.95-0.96 / 0.93-0.95 /
+//     0.93-0.94 / 0.96-0.97 / 1.00-1.01, residual with the nodes recorded 0.98-1.00 / 0.92-0.94 / 0.90-0.92 /
+//     0.91-0.93 / 0.95, accumulating 0.87-0.90; hidden 1024, 0.82-0.94, 0.85-0.94 and 0.85-0.91
+//   two rounds, 98304 / 114688 / 131072: 0.98-1.00 / 0.94 / 0.93-0.94 stored, 1.00-1.02 / 0.93-0.94 /
+//     0.91-0.93 residual, 1.05 / - / 0.97-0.98 accumulating; three 0.97-1.07 (163840 to 229376)
 //   depth 10, hidden 768, 49152 / 65536 / 69632 / 73728: 0.93-0.95 / 0.94-0.95 / 0.99-1.00 / 1.04-1.05
-//     stored, 1.00-1.01 / 0.95 / 0.97-0.98 / 0.99-1.00 residual with records
+//     stored, 1.00-1.01 / 0.93-0.94 / 0.95 / 0.99-1.00 residual
 //   depths 6 to 9 at 64 per leaf: hidden 768 1.09-1.13 (4096 tokens; 5120 0.95-0.97) / 0.97-1.00 /
 //     0.88-0.89 / 0.86-0.91, hidden 1024 1.31-1.34 / 1.16-1.19 / 1.05-1.21 / 0.97-1.07; at 96 per leaf
 //     hidden 1024 0.99-1.03 (6144 tokens) / 0.88-0.90 / 0.83-0.87 / 0.91-1.00

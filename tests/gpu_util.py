@@ -29,27 +29,32 @@ def run_fff(fff, L: dict, depth: int, trees: int, y_dtype: str, *, record=True, 
     else:
         y = torch.full((B, H), float("nan"), dtype=TORCH_DT[y_dtype], device=DEV)
     nodes = torch.full((B, trees, depth + 1), -7, dtype=torch.int32, device=DEV) if record else None
-    logits = torch.full((B, trees, depth + 1), float("nan"), dtype=torch.float32, device=DEV) if record else None
+    logits = (torch.full((B, trees, depth + 1), float("nan"), dtype=torch.float32, device=DEV)
+              if record and record != "nodes" else None)
     fff.forward(x, wi, wo, depth, trees, y, nodes_out=nodes, logits_out=logits, **kw)
     torch.cuda.synchronize()
     out = {"y": fff.to_numpy(y)}
     if record:
         out["nodes"] = nodes.cpu().numpy()
-        out["logits"] = logits.cpu().numpy()
+        if logits is not None:
+            out["logits"] = logits.cpu().numpy()
     return out
 
 
 def check_layer(fff, name: str, L: dict, depth: int, trees: int, y_dtype: str, act="gelu", tol=None,
-                max_conditioned: int = 0, **kw) -> dict:
+                max_conditioned: int = 0, record=True, **kw) -> dict:
     w_dtype = "bf16" if L["w_in"].dtype == np.uint16 else "f32"
     tol = tol if tol is not None else tol_for(w_dtype, y_dtype)
     B, H = L["x"].shape
     flush_print(f"[gpu] {name}: B={B} H={H} depth={depth} trees={trees} y={y_dtype} act={act} {kw}")
-    got = run_fff(fff, L, depth, trees, y_dtype, act=act, **kw)
+    got = run_fff(fff, L, depth, trees, y_dtype, act=act, record=record, **kw)
     ref = oracle.forward(L["x"], L["w_in"], L["w_out"], depth, trees, act=act)
     rep = parity.assert_parity(L["x"], L["w_in"], L["w_out"], depth, trees, ref, got["y"], got["nodes"],
                                tol=tol, act=act, max_conditioned=max_conditioned)
     # logits recorded by the device agree with fp64 along its own path wherever paths agree
+    if record == "nodes":
+        flush_print(f"[gpu] {name}: ok, {parity.summary(rep)}")
+        return rep
     same = (got["nodes"] == ref["nodes"])
     wmax = max(float(np.linalg.norm(parity.widen(L["w_in"][t]), axis=1).max()) for t in range(trees))
     scale = np.linalg.norm(parity.widen(L["x"]), axis=1)[:, None, None] * wmax

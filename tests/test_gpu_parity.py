@@ -991,7 +991,38 @@ def test_tiled_dense(fff_lib, H, D, B):
     plan = fff_lib.describe(x, wi, wo, D, 1, mode="tiled")  # the passes that run: a subtree pass, after a top pass
     assert "dense=1" in plan and plan.count("launch") == (1 if D == 5 else 2) and "emit" not in plan, plan
     assert f"top_levels={ {5: 0, 6: 3, 7: 4, 8: 4, 9: 5}.get(D, 6)} " in plan, plan
-    check_layer(fff_lib, f"tiled dense H={H} B={B} D={D}", L, D, 1, "bf16", mode="tiled")
+    check_layer(fff_lib, f"tiled dense H={H} B={B} D={D}", L, D, 1, "bf16", mode="tiled", record="nodes")
+
+
+def test_tiled_dense_is_the_default_at_the_throughput_batch(fff_lib):
+    w = WORKLOADS["d11_h768_b65536_bf16"]
+    L = synth.make_layer(w.seed, w.n_tokens, w.hidden, w.depth, w.n_trees, w.x_dtype, w.w_dtype)
+    x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
+    assert "dense=1" in fff_lib.describe(x, wi, wo, w.depth, 1)
+    check_layer(fff_lib, w.name, L, w.depth, w.n_trees, w.y_dtype, record="nodes")
+
+
+@pytest.mark.parametrize("D,B,act", [(5, 4096, "gelu_tanh"), (7, 8209, "identity"), (11, 49153, "gelu_tanh")])
+def test_tiled_dense_activations(fff_lib, D, B, act):
+    check_layer(fff_lib, f"tiled dense {act}", layer(303 + D, B, 768, D, 1, "bf16", "bf16"), D, 1, "bf16", act=act,
+                mode="tiled", record="nodes")
+
+
+@pytest.mark.parametrize("H,D,B", [(768, 5, 4111), (768, 7, 8200), (1024, 7, 12289), (768, 11, 49200)])
+def test_tiled_dense_small_integers_with_ties(fff_lib, H, D, B):
+    """Identity on sparse small integers: every product, sum and activation part is exact, many logits are zero
+    (a zero goes left), and y is the exact sum rounded to bf16 once."""
+    rng = np.random.default_rng(D)
+    N = (2 << D) - 1
+    cast = lambda shape, p: synth.as_dtype((rng.integers(-2, 3, shape) * (rng.random(shape) < p)).astype(np.float32), "bf16")
+    L = {"x": cast((B, H), 0.1), "w_in": cast((1, N, H), 0.05), "w_out": cast((1, N, H), 0.5)}
+    x, wi, wo = (fff_lib.from_numpy(L[k], DEV) for k in ("x", "w_in", "w_out"))
+    assert dense_of(fff_lib, x, wi, wo, D) == 1
+    got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", act="identity", record="nodes")
+    ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1, act="identity")
+    assert (ref["logits"][:, 0, :D] == 0).mean() > 0.05
+    assert np.array_equal(got["nodes"], ref["nodes"])
+    assert np.array_equal(synth.bf16_bits_to_f32(got["y"]), synth.bf16_bits_to_f32(synth.as_dtype(ref["y"].astype(np.float32), "bf16")))
 
 
 @pytest.mark.parametrize("H,D", [(128, 8), (896, 9)])
@@ -1015,6 +1046,9 @@ def test_tiled_dense_plan(fff_lib):
     assert dense_of(fff_lib, x, w, w, 11, y_dtype=torch.float32) == 0
     assert dense_of(fff_lib, x.float(), w, w, 11, y_dtype=torch.bfloat16) == 0
     assert dense_of(fff_lib, x, w, w, 11, norm="layernorm") == 0
+    # recorded nodes, not recorded logits
+    assert dense_of(fff_lib, x, w, w, 11, nodes_out=torch.empty((49152, 1, 12), dtype=torch.int32, device=DEV)) == 1
+    assert dense_of(fff_lib, x, w, w, 11, logits_out=torch.empty((49152, 1, 12), device=DEV)) == 0
     xw = torch.zeros(24576, 1024, dtype=torch.bfloat16, device=DEV)
     for d, n in ((6, 8192), (7, 12288), (8, 24576)):
         ww = torch.zeros(1, (2 << d) - 1, 1024, dtype=torch.bfloat16, device=DEV)
@@ -1054,7 +1088,7 @@ def test_tiled_dense_output_modes(fff_lib, D, B, out):
         fff_lib.forward(y, wi, wo, D, 1, y, nodes_out=nodes, mode="tiled", out="residual")
         got = {"y": fff_lib.to_numpy(y), "nodes": nodes.cpu().numpy()}
     else:
-        got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", out=out, y_init=y0 if out == "accumulate" else None)
+        got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", out=out, record="nodes", y_init=y0 if out == "accumulate" else None)
     ref = oracle.forward(L["x"], L["w_in"], L["w_out"], D, 1)
     parity.assert_parity(L["x"], L["w_in"], L["w_out"], D, 1, ref, got["y"], got["nodes"], tol=2e-2,
                          base_dev=y0 if out == "accumulate" else L["x"])
@@ -1063,7 +1097,7 @@ def test_tiled_dense_output_modes(fff_lib, D, B, out):
 def test_tiled_dense_token_chunks(fff_lib):
     """More tokens than one pair of passes takes (69632): chunks of equal size, every row written."""
     L = layer(320, 100003, 768, 6, 1, "bf16", "bf16")
-    check_layer(fff_lib, "tiled dense chunks", L, 6, 1, "bf16", mode="tiled")
+    check_layer(fff_lib, "tiled dense chunks", L, 6, 1, "bf16", mode="tiled", record="nodes")
 
 
 def test_tiled_dense_skewed_routing_deterministic(fff_lib):
@@ -1073,12 +1107,12 @@ def test_tiled_dense_skewed_routing_deterministic(fff_lib):
     x = synth.make_clustered_x(330, B, 768, "bf16", n_centres=5)
     wi, wo = synth.make_weights(330, 768, D, 1, "bf16")
     L = {"x": x, "w_in": wi, "w_out": wo}
-    check_layer(fff_lib, "tiled dense clustered", L, D, 1, "bf16", mode="tiled")
-    a = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled")
-    b = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled")
+    check_layer(fff_lib, "tiled dense clustered", L, D, 1, "bf16", mode="tiled", record="nodes")
+    a = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", record="nodes")
+    b = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", record="nodes")
     assert np.array_equal(a["y"], b["y"]) and np.array_equal(a["nodes"], b["nodes"])
-    c = run_fff(fff_lib, dict(L, x=np.ascontiguousarray(x[1001:51001])), D, 1, "bf16", mode="tiled")
-    assert np.array_equal(a["y"][1001:51001], c["y"]) and np.array_equal(a["logits"][1001:51001], c["logits"])
+    c = run_fff(fff_lib, dict(L, x=np.ascontiguousarray(x[1001:51001])), D, 1, "bf16", mode="tiled", record="nodes")
+    assert np.array_equal(a["y"][1001:51001], c["y"]) and np.array_equal(a["nodes"][1001:51001], c["nodes"])
 
 
 @pytest.mark.parametrize("B", [8207, 69632])
@@ -1089,11 +1123,11 @@ def test_tiled_dense_group_sizes(fff_lib, B):
     wi, wo = synth.make_weights(335, 768, D, 1, "bf16")
     x = np.concatenate([synth.make_clustered_x(335, B - B // 3, 768, "bf16", n_centres=2), synth.make_x(336, B // 3, 768, "bf16")])
     L = {"x": x, "w_in": wi, "w_out": wo}
-    check_layer(fff_lib, f"tiled dense groups B={B}", L, D, 1, "bf16", mode="tiled")
-    got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled")
+    check_layer(fff_lib, f"tiled dense groups B={B}", L, D, 1, "bf16", mode="tiled", record="nodes")
+    got = run_fff(fff_lib, L, D, 1, "bf16", mode="tiled", record="nodes")
     uniform = np.concatenate([synth.make_x(337, B - 1000, 768, "bf16"), x[:500], x[-500:]])
-    ref = run_fff(fff_lib, dict(L, x=uniform), D, 1, "bf16", mode="tiled")
-    for k in ("y", "nodes", "logits"):
+    ref = run_fff(fff_lib, dict(L, x=uniform), D, 1, "bf16", mode="tiled", record="nodes")
+    for k in ("y", "nodes"):
         assert np.array_equal(np.concatenate([got[k][:500], got[k][-500:]]), ref[k][-1000:]), k
 
 
@@ -1112,12 +1146,12 @@ def test_tiled_dense_non_finite_weights(fff_lib, D, B):
     bad["w_in"][0, leaf] = 0x7FC0       # nan
     bad["w_out"][0, leaf, ::2] = 0x7F80  # inf
     bad["w_out"][0, leaf, 1::2] = 0xFFC0
-    got = run_fff(fff_lib, dict(L, **bad), D, 1, "bf16", mode="tiled")
+    got = run_fff(fff_lib, dict(L, **bad), D, 1, "bf16", mode="tiled", record="nodes")
     parity.assert_parity(L["x"], L["w_in"], L["w_out"], D, 1, ref, got["y"], got["nodes"], tol=2e-2)
     visited = ref["nodes"][5, 0, D]
     one = {"w_in": L["w_in"], "w_out": L["w_out"].copy()}
     one["w_out"][0, visited, 7] = 0x7F80
-    got = run_fff(fff_lib, dict(L, **one), D, 1, "bf16", mode="tiled")
+    got = run_fff(fff_lib, dict(L, **one), D, 1, "bf16", mode="tiled", record="nodes")
     finite = np.isfinite(synth.bf16_bits_to_f32(got["y"]))
     hit = got["nodes"][:, 0, D] == visited
     assert hit.any() and not finite[hit, 7].any() and finite[~hit].all() and np.delete(finite[hit], 7, axis=1).all()
