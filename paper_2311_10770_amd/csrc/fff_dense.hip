@@ -397,12 +397,18 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_sub_kernel(Params p, Dens
         // (blockIdx % 8) takes a contiguous eighth of them, so that a group's rows are read through one L2
         const int cnt = s_cnt[lane];
         int lo16 = a.item / 16, hi16 = int(p.n_tokens) / a.item + (1 << s) <= a.round ? lo16 : TOK / 16;
+        const int cnt16 = (cnt + 15) / 16;
+        auto items_of = [&](int m) {  // ceil(cnt16 / m): exact, cnt16 <= 4352 and m <= 24
+            return int((uint32_t(cnt16 + m - 1) * ((1u << 20) / uint32_t(m) + 1)) >> 20);
+        };
         while (lo16 < hi16) {
-            const int most = (lo16 + hi16) / 2 * 16;
-            if (__builtin_amdgcn_readlane(wave_scan((cnt + most - 1) / most, lane), 63) <= a.round) hi16 = most / 16;
-            else lo16 = most / 16 + 1;
+            const int m = (lo16 + hi16) / 2;
+            if (int(group_sum<64>(float(items_of(m)))) <= a.round) hi16 = m;
+            else lo16 = m + 1;
+            lo16 = __builtin_amdgcn_readfirstlane(lo16);
+            hi16 = __builtin_amdgcn_readfirstlane(hi16);
         }
-        const int items = (cnt + 16 * lo16 - 1) / (16 * lo16);
+        const int items = items_of(lo16);
         const int incl = wave_scan(items, lane);
         const int total = __builtin_amdgcn_readlane(incl, 63);
         const int x = int(blockIdx.x % XCDS), i = int(blockIdx.x / XCDS);
@@ -716,6 +722,12 @@ size_t dense_workspace_bytes(int64_t n_tokens) {
 
 constexpr int DN_ITEM_MIN = 16 * DS_WAVES;  // a tile per wave
 
+// The least bound on a workgroup's tokens with which a round of workgroups can take the batch (a multiple of 16).
+static int dense_item_least(int64_t n_tokens, int cu_count) {
+    const int64_t mean = (n_tokens + cu_count - 1) / cu_count;
+    return int(std::min<int64_t>(std::max<int64_t>((mean + 15) / 16 * 16, DN_ITEM_MIN), DS_TOK));
+}
+
 // Tokens of a workgroup without a top pass (a multiple of 16): the batch over a number of workgroups that
 // fills the CUs.
 static int dense_item(int64_t n_tokens, int cu_count) {
@@ -785,7 +797,7 @@ hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t
         a.hist_ld = int32_t((wgs + 15) / 16 * 16);
         a.s = s;
         a.levels = sub;
-        a.item = s ? DN_ITEM_MIN : dense_item(c.n_tokens, cu_count);
+        a.item = s ? dense_item_least(c.n_tokens, cu_count) : dense_item(c.n_tokens, cu_count);
         a.round = cu_count;
         void* args[] = {&c, &a};
         Launch L[2];
