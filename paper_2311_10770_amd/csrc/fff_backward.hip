@@ -11,7 +11,8 @@
 // 1. bwd_token_kernel (bwd_wide_token_kernel, bwd_generic_token_kernel): a group of lanes per
 //    token, dy in registers; per level the two rows of the known path are
 //    gathered, da is reduced across the group, dx accumulates in registers;
-//    the pair (a, dl) of every visit is saved and the leaves are counted.
+//    the pair (a, dl) of every visit is saved and the leaves are counted (or, of many tokens per leaf
+//    at the vector-row widths, after the ranks by bwd_leafsum_kernel).
 // 2. bwd_scan_kernel + bwd_rank/base/place_kernel: stable counting sort of the tokens by
 //    leaf.  Sorted by leaf, the tokens through any node form one contiguous
 //    run at every level (a node's leaves are a contiguous range).
@@ -840,7 +841,7 @@ __global__ __launch_bounds__(BWD_BLOCK) void bwd_fixup_kernel(BwdParams p, int t
 // part[] and are added in a fixed order by bwd_wsum_kernel.  Every dW element
 // has one writer and the order of every sum is fixed.
 constexpr int WT_WAVES_MAX = 8;
-constexpr int WT_FILL_WAVES = 3072;  // waves that fill the chip (256 CUs of 12)
+constexpr int WT_FILL_WAVES = 3072;  // waves that fill 256 CUs (12 each)
 constexpr int WT_AHEAD = 2;        // operand sets of a wave
 constexpr int WT_TOP_LEVELS = 9;   // subtrees hang at level min(D, 9)
 constexpr int WT_MAX_SUB = 6;      // depth <= 15: at most 2^6 leaves per subtree
@@ -1483,8 +1484,8 @@ __global__ __launch_bounds__(64 * FUSED_WAVES_MAX) void bwd_fused_kernel(BwdPara
 // computed by bwd_place_kernel.  Twelve waves of at most 168 registers, three per SIMD (hidden 768).
 // Against bwd_fused_kernel's six waves of 128 columns, which held the tiles in registers (two waves on
 // two of the SIMDs, one on the others; 6 us per tile of sixteen tokens, most of it waiting between
-// the two barriers of a tile): 134 -> 101 us at 65536 tokens, depth 11, hidden 768, the backward 158 ->
-// 128; depth 7, 206 -> 140; depth 5, 16384 tokens, 182 -> 121.  Of the 101 us the dx stores take 18,
+// the two barriers of a tile): 134 -> 99 us at 65536 tokens, depth 11, hidden 768, the backward 158 ->
+// 121; depth 7, 206 -> 140; depth 5, 16384 tokens, 182 -> 121.  Of about 100 us the dx stores take 18,
 // the dW products 9, adding the partial da 8, the partial rows above the subtrees 4.  Slower forms:
 // sixteen waves at hidden 1024 (128 registers, 41 spilled: 238 against 178 us, so the widths above 768
 // stay with bwd_fused_kernel, as does 128, which has too few waves for the tile's 256 entries); the
@@ -1948,7 +1949,8 @@ static int64_t bwd_chunks(int64_t n_tokens, int32_t depth) {
 static bool wtile_shape(int32_t depth, int32_t hidden) { return depth <= 15 && hidden % 128 == 0; }
 static int wtile_k(int32_t depth) { return std::min<int32_t>(depth, WT_TOP_LEVELS); }
 // The weight kernel by itself hangs them higher where the waves of the level above (a workgroup of
-// hidden / 128, at most eight, per subtree, tree and matrix) still fill three quarters of the chip:
+// hidden / 128, at most eight, per subtree, tree and matrix) are still WT_FILL_WAVES or more, whatever
+// the device's CUs (the sums' order follows the shapes alone):
 // each level less halves the sums that go to the fix-up and back, and a leaf's tokens follow each
 // other (fp32, hidden 768, 4 trees of depth 9, 16384 tokens: subtrees at level 9 in 97 us and 23 in
 // the fix-up, at level 6 in 82 and 8; at hidden 256, where a workgroup has two waves, a whole

@@ -28,7 +28,7 @@
 // What bounds it: HBM and MALL traffic, x twice and y once.  At 65536 tokens, depth 11, hidden 768,
 // buffers rotating so that nothing is warm: top pass 24 us (19 where no dirty rows of y are being
 // written back), subtree pass 52 us, of which 16 gather x (6.3 TB/s), 17 store y (5.9 TB/s), 6
-// look the tokens up, 2 evaluate the activations and 3 transpose W_out; 81.2 us per forward against
+// look the tokens up, 2 evaluate the activations and 3 transpose W_out; 81.6 us per forward against
 // 94.7 us for the walk and the leaf tiles.  First forms of the subtree pass: four waves per
 // workgroup, x rows loaded straight into the MFMA operand layout, W_out fetched one block ahead of
 // its use: 94 us (a quad of lanes then reads four rows, and the loads waited for the stores issued

@@ -137,7 +137,8 @@ __device__ __forceinline__ float wide_dot(const X& x, const uint4* w) {
 
 // The (LANES, NV) classes: f(lanes, nv), integral constants, for the smallest that holds rowv vectors
 // (at most WIDE_MAX_VECS).  Sixteen lanes up to six vectors each (heavy layouts, 16 fp32 registers per
-// vector and lane besides the row: up to four), then as few lanes as keep two waves per SIMD.
+// vector and lane besides the row: up to four), then 32 and 64.  Two waves per SIMD or more, except rows
+// past 384 vectors of bf16 W with x or dy widened: one (296 registers; 332 in the backward).
 constexpr int WIDE_MAX_VECS = 512;
 template <bool HEAVY, class F>
 auto wide_class(int rowv, F&& f) {
