@@ -69,7 +69,7 @@ struct DenseArgs {
     int32_t top_wgs;
     int32_t s;         // levels of the top pass (0: none)
     int32_t levels;    // levels of the subtree pass
-    int32_t item;      // most tokens of a subtree workgroup (s == 0), or the fewest such bound
+    int32_t item;      // most tokens of a subtree workgroup (s == 0), or the least such bound
     int32_t round;     // subtree workgroups that run at once
     float* act;        // [B, DN_REC] activations of levels s .. D and, last, the subtree column of the leaf
 };
@@ -390,19 +390,18 @@ __global__ __launch_bounds__(DS_THREADS, 2) void dense_sub_kernel(Params p, Dens
             if ((tid & 7) == 0) s_cnt[gg] = int32_t(sum);
         }
         __syncthreads();
-        // items: ceil(count / most) per group, groups in order, with the smallest bound (a multiple of 16)
-        // whose items all run at once: the groups' sizes are the routing's, and one item more than the
-        // CUs take would cost a second round (bounds from the mean size, an eighth to spare: depth 11,
+        // items: ceil(count / most) per group, groups in order, with the smallest bound (a multiple of 16, from
+        // a.item up) whose items all run at once: the groups' sizes are the routing's, and one item more than
+        // the CUs take would cost a second round (a.item alone, an eighth over the mean: depth 11,
         // hidden 768, 57344 / 61440 / 65536 tokens 102 / 107 / 80 us a forward; so 75 / 78 / 82).  XCD x
         // (blockIdx % 8) takes a contiguous eighth of them, so that a group's rows are read through one L2
         const int cnt = s_cnt[lane];
-        int lo16 = a.item / 16, hi16 = int(p.n_tokens) / a.item + (1 << s) <= a.round ? lo16 : TOK / 16;
+        int lo16 = a.item / 16, hi16 = TOK / 16;
         const int cnt16 = (cnt + 15) / 16;
-        auto items_of = [&](int m) {  // ceil(cnt16 / m): exact, cnt16 <= 4352 and m <= 24
-            return int((uint32_t(cnt16 + m - 1) * ((1u << 20) / uint32_t(m) + 1)) >> 20);
+        auto items_of = [&](int m) {  // ceil(cnt16 / m): the quotient is 0.5 / m or more from the next integer
+            return int((float(cnt16 + m - 1) + 0.5f) * __builtin_amdgcn_rcpf(float(m)));
         };
-        while (lo16 < hi16) {
-            const int m = (lo16 + hi16) / 2;
+        for (int m = lo16; lo16 < hi16; m = (lo16 + hi16) / 2) {  // the first bound fits as a rule
             if (int(group_sum<64>(float(items_of(m)))) <= a.round) hi16 = m;
             else lo16 = m + 1;
             lo16 = __builtin_amdgcn_readfirstlane(lo16);
@@ -722,10 +721,13 @@ size_t dense_workspace_bytes(int64_t n_tokens) {
 
 constexpr int DN_ITEM_MIN = 16 * DS_WAVES;  // a tile per wave
 
-// The least bound on a workgroup's tokens with which a round of workgroups can take the batch (a multiple of 16).
-static int dense_item_least(int64_t n_tokens, int cu_count) {
-    const int64_t mean = (n_tokens + cu_count - 1) / cu_count;
-    return int(std::min<int64_t>(std::max<int64_t>((mean + 15) / 16 * 16, DN_ITEM_MIN), DS_TOK));
+// The least bound on a subtree workgroup's tokens (a multiple of 16): the mean group over as many workgroups as
+// fill the CUs, with an eighth to spare for the usual spread of the groups' sizes.
+static int dense_item_least(int64_t n_tokens, int s, int cu_count) {
+    const double mean = double(n_tokens) / double(int64_t(1) << s);
+    const int64_t per = std::max<int64_t>(1, cu_count >> s);  // workgroups per group
+    const int64_t item = int64_t(mean * 1.125 / double(per) / 16.0 + 1.0) * 16;
+    return int(std::min<int64_t>(std::max<int64_t>(item, DN_ITEM_MIN), DS_TOK));
 }
 
 // Tokens of a workgroup without a top pass (a multiple of 16): the batch over a number of workgroups that
@@ -797,7 +799,7 @@ hipError_t run_dense(const Params& p, void* workspace, int cu_count, hipStream_t
         a.hist_ld = int32_t((wgs + 15) / 16 * 16);
         a.s = s;
         a.levels = sub;
-        a.item = s ? dense_item_least(c.n_tokens, cu_count) : dense_item(c.n_tokens, cu_count);
+        a.item = s ? dense_item_least(c.n_tokens, s, cu_count) : dense_item(c.n_tokens, cu_count);
         a.round = cu_count;
         void* args[] = {&c, &a};
         Launch L[2];
