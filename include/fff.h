@@ -76,7 +76,8 @@ typedef enum { FFF_ACT_GELU_ERF = 0, FFF_ACT_GELU_TANH = 1, FFF_ACT_IDENTITY = 2
  * With 2, 4 or 8 trees (GROUPED and TILED) each walk workgroup walks the tree
  * of its XCD, with that tree's top levels in LDS.
  * GENERIC: any hidden size; rows of whole 16-byte vectors as a fused descent
- * with the row length as a run-time value, other rows a wave per token.
+ * with the row length as a run-time value; other rows, and many trees of a
+ * single node over rows of at most 64 elements, a wave per token.
  * TILED (large batches of bf16 x, W and y through one tree of depth at most 11,
  * hidden 768 or 1024, without logits_out and a request for lds_levels, take the
  * tree's subtrees as dense products on MFMA instead of what follows):
